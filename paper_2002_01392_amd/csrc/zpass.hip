@@ -936,26 +936,6 @@ __global__ __launch_bounds__(ZNT, 2) void k_z_pass_batch(const ZPassDesc* d, int
                                ((long long)blockIdx.x - D.wg0) * ZPB, threadIdx.x, coef, gam_s);
 }
 
-// ---------------------------------------------------------------- fc_extend
-// Strided real lines, one thread per line.
-__global__ __launch_bounds__(256) void k_fc_extend(const double* __restrict__ in, long long nlines,
-                                                   long long ips, long long ils,
-                                                   double* __restrict__ out, long long ops,
-                                                   long long ols, int nz, int C, int d,
-                                                   const double* __restrict__ M) {
-  const long long line = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (line >= nlines) return;
-  const double* f = in + line * ils;
-  double* o = out + line * ols;
-  for (int s = 0; s < nz; ++s) o[s * ops] = f[s * ips];
-  for (int i = 0; i < C; ++i) {
-    double acc = 0.0;
-    for (int j = 0; j < d; ++j) acc += M[i * d + j] * f[(nz - d + j) * ips];
-    for (int j = 0; j < d; ++j) acc += M[(C - 1 - i) * d + (d - 1 - j)] * f[j * ips];
-    o[(nz + i) * ops] = acc;
-  }
-}
-
 // ---------------------------------------------------------------- fc_derivative
 // Two real lines per complex line (line 2q real part, 2q+1 imaginary part):
 // the multipliers i k~z (Nyquist zeroed) and -kz^2 map real lines to real
@@ -1187,15 +1167,6 @@ void launch_z_pass(const ZArgs& a, bool big, const StageAArgs& sa, const StageBA
       FCNS_LAUNCH((k_z_pass<DynPlan<false>, 9, false>), grid, dim3(ZNT), sh, st, a, sa, sb, zb,
                   nfields);
   }
-}
-
-void launch_fc_extend(const double* in, long long nlines, long long ips, long long ils, double* out,
-                      long long ops, long long ols, int nz, int C, int d, const double* M,
-                      hipStream_t st) {
-  const int nt = 256;
-  dim3 grid((unsigned)((nlines + nt - 1) / nt));
-  FCNS_LAUNCH(k_fc_extend, grid, dim3(nt), 0, st, in, nlines, ips, ils, out, ops, ols, nz,
-                     C, d, M);
 }
 
 void launch_fc_derivative(const ZArgs& a, bool big, const double* in, double* out,
