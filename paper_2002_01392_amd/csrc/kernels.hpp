@@ -131,6 +131,11 @@ bool z_pass_fits(const ZArgs& a);
 void launch_z_pass(const ZArgs& a, bool big, const StageAArgs& sa, const StageBArgs& sb,
                    const ZBackArgs& zb, int nfields, hipStream_t st);
 
+// fc_derivative of contiguous lines, N' = 32 K (zwave.hip)
+bool zw_deriv_fits(const ZArgs& a, long long ps);
+void launch_zw_deriv(const ZArgs& a, const double* in, double* out, long long nlines,
+                     long long ls, int order, hipStream_t st);
+
 // One launch of the fused z pass over several problems (device array of n
 // descriptors; wg0 = first workgroup of each problem, ascending from 0;
 // groups = total workgroups).  Every problem runs the run-time plan engine

@@ -2,7 +2,7 @@
 // allocation: the transform's twiddle table and the continuation matrix are
 // staged in a file-scope device array instead of context buffers.
 //
-// The array `scratch` holds, per call, [twiddles: tsize complex128][M: C*d
+// The array `scratch` holds, per call, [twiddles: tsize complex128, then the N' roots][M: C*d
 // float64].  Host code never passes its name to a kernel: on each device the
 // address comes from hipGetSymbolAddress, taken once with that device current
 // and kept per device.  Every call on a device shares that device's array, so
@@ -48,7 +48,9 @@ struct NAMatrix {
 // Twiddles of the Stockham plan (the same layout as the context's table: per
 // stage with ns > 1 the factors exp(-2 pi i m k / (ns R)) as [m-1][k], per
 // odd radix its R roots), and M, into the scratch.
-__global__ void k_noalloc_tables(FFTPlan pl, NAMatrix mat, cpx<double>* tw, double* M) {
+// roots (null: none): the pl.n roots exp(-2 pi i q / n).
+__global__ void k_noalloc_tables(FFTPlan pl, NAMatrix mat, cpx<double>* tw, double* M,
+                                 cpx<double>* roots) {
   const int tid = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
   long long ns = 1;
   for (int s = 0; s < pl.nst; ++s) {
@@ -74,6 +76,12 @@ __global__ void k_noalloc_tables(FFTPlan pl, NAMatrix mat, cpx<double>* tw, doub
   }
   if (pl.nst == 1 && pl.toff[0] < 0 && pl.coff[0] < 0 && tid == 0)
     tw[0] = mk(1.0, 0.0);   // a plan without factors keeps one unused entry
+  if (roots)
+    for (int q = tid; q < pl.n; q += nt) {
+      double sn, cs;
+      sincospi(-2.0 * (double)q / (double)pl.n, &sn, &cs);
+      roots[q] = mk(cs, sn);
+    }
   for (int i = tid; i < mat.n; i += nt) M[i] = mat.m[i];
 }
 
@@ -160,7 +168,10 @@ extern "C" fcns_status fcns_fc_derivative_noalloc(int32_t nz, double lz, int32_t
       mat.m[i * fc_d + j] = (double)acc;
     }
   hipStream_t stream = (hipStream_t)hip_stream;
-  hipLaunchKernelGGL(k_noalloc_tables, dim3(4), dim3(256), 0, stream, pl, mat, tw, M);
+  // (the roots serve the wavefront kernel, which the launcher takes where it
+  // fits; lengths whose plan table leaves no room for them run without)
+  cpx<double>* roots = pl.tsize + npr <= NA_MAX_TW ? tw + pl.tsize : nullptr;
+  hipLaunchKernelGGL(k_noalloc_tables, dim3(4), dim3(256), 0, stream, pl, mat, tw, M, roots);
   if (hipGetLastError() != hipSuccess) return FCNS_EDEVICE;
   ZArgs a{};
   Geom& g = a.g;
@@ -174,6 +185,7 @@ extern "C" fcns_status fcns_fc_derivative_noalloc(int32_t nz, double lz, int32_t
   g.kzs = 2.0 * M_PI / g.lzp;
   a.pl = pl;
   a.tw = tw;
+  a.tw64 = roots;
   a.fc = M;
   a.nonfinite = nullptr;
   launch_fc_derivative(a, big, in, out, nlines, ps, ls, order, stream);

@@ -1172,6 +1172,10 @@ void launch_z_pass(const ZArgs& a, bool big, const StageAArgs& sa, const StageBA
 void launch_fc_derivative(const ZArgs& a, bool big, const double* in, double* out,
                           long long nlines, long long ps, long long ls, int order,
                           hipStream_t st) {
+  if (zw_deriv_fits(a, ps)) {
+    launch_zw_deriv(a, in, out, nlines, ls, order, st);
+    return;
+  }
   const long long nq = (nlines + 1) / 2;
   dim3 grid((unsigned)((nq + ZPB - 1) / ZPB));
   const size_t sh = zshared_bytes<double>(a.g, a.pl.tsize);

@@ -87,3 +87,44 @@ def test_fc_extend_strides_and_tables(fcns, nz, d, C, n, ins, outs):
     gaps[idx.ravel()] = False
     assert np.all(got[gaps] == 7.0)
     s.close()
+
+
+# N' = 32 K (K = 2..9): four lines per wave, sixteen per workgroup; 1, 2, 3, 17 and
+# 35 lines leave partial pairs, waves and workgroups.  C = 31, 25, 15 put
+# 31, 25, 15 continuation rows into the last register.
+@pytest.mark.parametrize("npr,C,n", [(64, 31, 1), (96, 25, 2), (128, 15, 3), (160, 31, 17),
+                                     (192, 25, 35), (224, 31, 16), (256, 15, 33),
+                                     (288, 31, 35), (288, 25, 5), (64, 32, 7)])
+@pytest.mark.parametrize("order", [1, 2])
+def test_fc_derivative_wavefront_lengths(fcns, npr, C, n, order):
+    nz, d = npr - C, 5
+    table = None
+    if C == 32:   # (no stored table: a smooth one, M = 0 but for the end values)
+        q, a = np.eye(d), np.zeros((C, d))
+        a[:, d - 1] = np.linspace(1.0, 0.0, C + 2)[1:-1] ** 2
+        table = np.concatenate([q.ravel(), a.ravel()])
+    s = fcns.Solver(8, 8, nz, 1.0, 1.0, 1.7, 0.0, d=d, C=C, table=table)
+    f = _lines(nz, n, 3 * npr + n)
+    if table is None:
+        ref = fc_derivative_lines(f, d, C, 1.7, order)
+    else:
+        op = FCGram(nz, d, 31, 1.7)   # its wavenumber rule, this table and length
+        op.Mr, op.Ml = a, a[::-1, ::-1].copy()
+        op.C, op.np_ = C, npr
+        op.lzp = npr * op.dz
+        lbar = np.where(2 * np.arange(npr) < npr, np.arange(npr), np.arange(npr) - npr)
+        op.kz = 2 * np.pi * lbar / op.lzp
+        op.kz_odd = op.kz.copy()
+        op.kz_odd[npr // 2] = 0.0
+        ref = op.derivative(f.T, order).T
+    for ps, ls in ((1, nz), (1, nz + 5), (n, 1), (2, 2 * nz + 1)):
+        src, idx = _strided(f, ps, ls)
+        dst = torch.full_like(src, 7.0)
+        assert s.lib.fcns_fc_derivative(s.ctx, order, _p(src), n, ps, ls, _p(dst)) == 0
+        torch.cuda.synchronize()
+        got = dst.cpu().numpy()
+        assert rel_l2(got[idx], ref) < 1e-11, (ps, ls)
+        gaps = np.ones(got.size, bool)
+        gaps[idx.ravel()] = False
+        assert np.all(got[gaps] == 7.0), (ps, ls)
+    s.close()
