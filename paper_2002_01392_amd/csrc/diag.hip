@@ -78,6 +78,39 @@ __global__ __launch_bounds__(DNT) void k_spectra(Geom g, const cpx<double>* __re
   }
 }
 
+// One continued field between its pencil groups (spec_base) and the caller's
+// complex128 [N'][ny][nkx] (8-byte aligned), one thread per coefficient.
+template <bool GET>
+__global__ __launch_bounds__(DNT) void k_spec_copy(Geom g, cpx<double>* __restrict__ spec,
+                                                   double* __restrict__ rows) {
+  const long long e = (long long)blockIdx.x * DNT + threadIdx.x;
+  const int ix = (int)(e % g.nkx);
+  const long long r = e / g.nkx;   // l ny + iy
+  const int iy = (int)(r % g.ny);
+  const long long l = r / g.ny;
+  if (l >= g.npr) return;
+  cpx<double>& c = spec[spec_base(g, (long long)iy * g.nkxp + ix) + SPEC_ROW * l];
+  if constexpr (GET) {
+    rows[2 * e] = c.x;
+    rows[2 * e + 1] = c.y;
+  } else {
+    c = mk(rows[2 * e], rows[2 * e + 1]);
+  }
+}
+
+static dim3 spec_grid(const Geom& g) {
+  const long long n = (long long)g.npr * g.ny * g.nkx;
+  return dim3((unsigned)((n + DNT - 1) / DNT));
+}
+void launch_spec_get(const Geom& g, const cpx<double>* spec, double* rows, hipStream_t st) {
+  hipLaunchKernelGGL(k_spec_copy<true>, spec_grid(g), dim3(DNT), 0, st, g,
+                     const_cast<cpx<double>*>(spec), rows);
+}
+void launch_spec_set(const Geom& g, const double* rows, cpx<double>* spec, hipStream_t st) {
+  hipLaunchKernelGGL(k_spec_copy<false>, spec_grid(g), dim3(DNT), 0, st, g, spec,
+                     const_cast<double*>(rows));
+}
+
 void launch_diag_planes(const Geom& g, const cpx<double>* mv, long long ms, int nf, double* out,
                         hipStream_t st) {
   hipLaunchKernelGGL(k_diag_planes, dim3(g.nz), dim3(DNT), 0, st, g, mv, ms, nf, out);

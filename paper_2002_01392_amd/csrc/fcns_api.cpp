@@ -1596,12 +1596,8 @@ extern "C" fcns_status fcns_get_spectral(fcns_ctx* c, int32_t field, double* out
   if (!c) return FCNS_EINVAL;
   if (!c->has_state) return fail(c, FCNS_ESTATE, "no state");
   if (field < 0 || field >= c->nf || !out) return fail(c, FCNS_EINVAL, "bad field or NULL");
-  const size_t w = c->g.nkx * sizeof(cpx<double>), ld = c->g.nkxp * sizeof(cpx<double>);
-  return check_hip(c,
-                   hipMemcpy2DAsync(out, w, c->P + field * c->S, ld, w,
-                                    (size_t)c->g.npr * c->g.ny, hipMemcpyDeviceToDevice,
-                                    c->stream),
-                   "get_spectral");
+  launch_spec_get(c->g, c->P + field * c->S, out, c->stream);
+  return check_launch(c, "get_spectral");
 }
 
 extern "C" fcns_status fcns_set_spectral(fcns_ctx* c, const double* const* fields,
@@ -1610,12 +1606,8 @@ extern "C" fcns_status fcns_set_spectral(fcns_ctx* c, const double* const* field
   if (!fields) return fail(c, FCNS_EINVAL, "NULL fields");
   for (int f = 0; f < c->nf; ++f) {
     if (!fields[f]) return fail(c, FCNS_EINVAL, "NULL field");
-    const size_t w = c->g.nkx * sizeof(cpx<double>), ld = c->g.nkxp * sizeof(cpx<double>);
-    fcns_status st = check_hip(c,
-                               hipMemcpy2DAsync(c->P + f * c->S, ld, fields[f], w, w,
-                                                (size_t)c->g.npr * c->g.ny,
-                                                hipMemcpyDeviceToDevice, c->stream),
-                               "set_spectral");
+    launch_spec_set(c->g, fields[f], c->P + f * c->S, c->stream);
+    fcns_status st = check_launch(c, "set_spectral");
     if (st != FCNS_OK) return st;
   }
   if (wall_grad) {

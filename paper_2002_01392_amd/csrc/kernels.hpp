@@ -189,6 +189,10 @@ void launch_diag_planes(const Geom& g, const cpx<double>* mv, long long ms, int 
 void launch_spectra(const Geom& g, const cpx<double>* q, int z, double* ex, double* ey,
                     hipStream_t st);
 
+// one continued field between its pencil groups and [N'][ny][nkx] rows
+void launch_spec_get(const Geom& g, const cpx<double>* spec, double* rows, hipStream_t st);
+void launch_spec_set(const Geom& g, const double* rows, cpx<double>* spec, hipStream_t st);
+
 // small helpers
 void launch_fill(cpx<double>* p, long long n, hipStream_t st);
 void launch_sub_mean00(cpx<double>* pmix, long long npen, int nz, double scale, hipStream_t st);

@@ -3,9 +3,9 @@
 // pressure projection with its closed-form homogeneous part.
 //
 // Data layout (complex, x fastest): mixed (kx, ky, z) fields are
-// [nz][ny][nkxp], continued spectral (kx, ky, kz) fields are [N'][ny][nkxp],
-// with the kx row padded to nkxp (a multiple of 4, so that 4-line tiles of
-// the y pass are 64-byte aligned).  A pencil is one (kx, ky) pair,
+// [nz][ny][nkxp], continued spectral (kx, ky, kz) fields are in groups of 8
+// pencils, [npen / 8][N'][8] (spec_base), with the kx row padded to nkxp (a
+// multiple of 4, so that 4-line tiles of the y pass are 64-byte aligned).  A pencil is one (kx, ky) pair,
 // p = ky * nkxp + kx; slots with kx >= nkx are padding and never touched.  A
 // workgroup owns ZPB consecutive pencils and stages their lines in LDS as
 // X[l * ZPB + pb] (pencil index fastest), so every global row access is ZPB
@@ -225,7 +225,7 @@ __global__ __launch_bounds__(ZNT) void k_z_fwd(ZArgs a, const cpx<double>* __res
   for (int l = lt; l < g.npr; l += ZLS) {
     cpx<double> v = cvt<double>(R[l * ZPB + pb]);
     if (filter) v = v * (a.sigz[l] * sxy);
-    dst[(long long)l * g.npen + p] = v;
+    dst[spec_base(g, p) + SPEC_ROW * l] = v;
   }
 }
 
@@ -293,15 +293,15 @@ __device__ __forceinline__ void load_rows(const ZArgs& a, const cpx<double>* src
   const Geom& g = a.g;
   const int npr = FP::dynamic ? g.npr : FP::n;
   const int pb = tid % ZPB, lt = tid / ZPB;
-  const long long p = p0 + pb;
+  const long long p = p0 + pb, sp = spec_base(g, p);
   const bool pv = pencil_valid(g, p);
 #pragma unroll
   for (int r = 0; r < OWN; ++r) {
     const int l = lt + r * ZLS;
     if constexpr (NT)
-      keep[r] = (pv && l < npr) ? ld_stream(src + (long long)l * g.npen + p) : zero<double>();
+      keep[r] = (pv && l < npr) ? ld_stream(src + sp + SPEC_ROW * l) : zero<double>();
     else
-      keep[r] = (pv && l < npr) ? src[(long long)l * g.npen + p] : zero<double>();
+      keep[r] = (pv && l < npr) ? src[sp + SPEC_ROW * l] : zero<double>();
   }
 }
 
@@ -404,7 +404,7 @@ __device__ __forceinline__ void z_stageA_field(const ZLds<T>& L, const ZArgs& a,
       return *q;
   };
   cpx<TM> nr[OWN];
-  const long long pc = pv ? p : 0;
+  const long long pc = pv ? p : 0, sp = spec_base(g, pc);
   if (nl_in) {
 #pragma unroll
     for (int r = 0; r < OWN; ++r) nr[r] = nl_in[r];
@@ -424,7 +424,7 @@ __device__ __forceinline__ void z_stageA_field(const ZLds<T>& L, const ZArgs& a,
 #pragma unroll
   for (int r = 0; r < OWN; ++r) {
     const int l = min(lt + r * ZLS, npr - 1);  // rows past N' are never used
-    const long long gi = (long long)l * g.npen + pc;
+    const long long gi = sp + SPEC_ROW * l;
     vtr[r] = ld(vt + gi);
     if constexpr (!WV) wr[r] = ld(w + gi);
     sgr[r] = a.sigz[l];
@@ -453,7 +453,7 @@ __device__ __forceinline__ void z_stageA_field(const ZLds<T>& L, const ZArgs& a,
     if (wbuoy) {
 #pragma unroll
       for (int r = 0; r < OWN; ++r)
-        bsr[r] = ld(wbuoy + (long long)min(lt + r * ZLS, npr - 1) * g.npen + pc);
+        bsr[r] = ld(wbuoy + sp + SPEC_ROW * min(lt + r * ZLS, npr - 1));
     }
   }
 #pragma unroll
@@ -523,7 +523,7 @@ __device__ __forceinline__ void z_stageA_field(const ZLds<T>& L, const ZArgs& a,
   if (cs_out) {
 #pragma unroll
     for (int r = 0; r < OWN; ++r)
-      cs_out[r] = cs_next[(long long)min(lt + r * ZLS, npr - 1) * g.npen + pc];
+      cs_out[r] = cs_next[sp + SPEC_ROW * min(lt + r * ZLS, npr - 1)];
   }
   __syncthreads();
   R = fft_run<T, ZPB, ZNT, false, FP>(L.X0, L.X1, ZPB, 1, a.pl, L.tw, tid);
@@ -542,7 +542,7 @@ __device__ __forceinline__ void z_stageA_field(const ZLds<T>& L, const ZArgs& a,
       for (int r = 0; r < OWN; ++r)
         if (lt + r * ZLS < npr) {
           // (not read again by the workgroup)
-          cpx<double>* o = out + (long long)(lt + r * ZLS) * g.npen + p;
+          cpx<double>* o = out + sp + SPEC_ROW * (lt + r * ZLS);
           if constexpr (NT)
             st_stream(o, keep[r]);
           else
@@ -558,9 +558,9 @@ __device__ __forceinline__ void z_stageA_field(const ZLds<T>& L, const ZArgs& a,
       for (int r = 0; r < OWN; ++r) ov[r] = cvt<double>(R[min(lt + r * ZLS, npr - 1) * ZPB + pb]);
 #pragma unroll
       for (int r = 0; r < OWN; ++r)
-        if (lt + r * ZLS < npr) out[(long long)(lt + r * ZLS) * g.npen + p] = ov[r];
+        if (lt + r * ZLS < npr) out[sp + SPEC_ROW * (lt + r * ZLS)] = ov[r];
     } else {
-      for (int l = lt; l < npr; l += ZLS) out[(long long)l * g.npen + p] = cvt<double>(R[l * ZPB + pb]);
+      for (int l = lt; l < npr; l += ZLS) out[sp + SPEC_ROW * l] = cvt<double>(R[l * ZPB + pb]);
     }
   }
 }
@@ -611,6 +611,7 @@ __device__ __forceinline__ void z_stageB_body(const ZLds<T>& L, const ZArgs& a,
   const int pb_me = tid % ZPB, lt = tid / ZPB;
   const long long p_me = p0 + pb_me;
   const bool valid_me = pencil_valid(g, p_me);
+  const long long sp_me = spec_base(g, valid_me ? p_me : 0);
   ZTables<T> tab{};
   if (tables) tab = ztab_load<T>(a, tid);
   const cpx<double>* gtw = a.tw64;
@@ -641,8 +642,7 @@ __device__ __forceinline__ void z_stageB_body(const ZLds<T>& L, const ZArgs& a,
       etr[r] = conj(gtw[ei]);
 #pragma unroll
     for (int r = 0; r < HOLD; ++r) {
-      const long long gi =
-          valid_me ? (long long)min(lt + r * ZLS, npr - 1) * g.npen + p_me : 0;
+      const long long gi = sp_me + SPEC_ROW * min(lt + r * ZLS, npr - 1);
 #pragma unroll
       for (int i = 0; i < 3; ++i) hv[i][r] = (i == KF) ? kv[r] : (i == KP) ? kp[r] : s.vs[i][gi];
     }
@@ -660,7 +660,7 @@ __device__ __forceinline__ void z_stageB_body(const ZLds<T>& L, const ZArgs& a,
         V1 = hv[1][r];
         V2 = hv[2][r];
       } else {
-        const long long gi = (long long)l * g.npen + p_me;
+        const long long gi = sp_me + SPEC_ROW * l;
         V0 = s.vs[0][gi];
         V1 = s.vs[1][gi];
         V2 = s.vs[2][gi];
@@ -762,7 +762,7 @@ __device__ __forceinline__ void z_stageB_body(const ZLds<T>& L, const ZArgs& a,
       if (pm) Xo[e] = zero<T>();
       continue;
     }
-    const long long gi = (long long)l * g.npen + p_me;
+    const long long gi = sp_me + SPEC_ROW * l;
     cpx<double> V0, V1, V2;
     if constexpr (HOLD > 0) {
       V0 = hv[0][r];
