@@ -186,11 +186,11 @@ fcns_status fcns_batch_step(fcns_ctx* const* ctxs, int32_t n, const double* dts,
  * different shapes allowed, N' <= 288 each, the same rk_order) and their
  * time steps (HOST, copied).  fcns_batch_run advances every member nsteps
  * steps: each context's x and y passes run on its own stream, and in every
- * stage whose output buffer is not its input (both stages of o = 2) one
- * kernel runs the fused z pass (continuation, z transforms, RK combine,
- * projection, back transforms) of all members together, workgroup by
- * workgroup over their pencil groups, on a stream of the batch; each member
- * waits for it before its next pass.  Each member's result matches its own
+ * stage that runs the fused z pass (see fcns_set_z_fused) one kernel runs it
+ * (continuation, z transforms, RK combine, projection, back transforms) for
+ * all members together, workgroup by workgroup over their pencil groups, on a
+ * stream of the batch (members of N' = 32 K: one kernel per length, the
+ * others one for all); each member waits for it before its next pass.  Each member's result matches its own
  * fcns_rk_step with the fused z pass to rounding (the same per-workgroup
  * code).  The batch reads its members' parameters, tables and buffers at
  * every run (a member retuned or given new parameters is picked up).
@@ -215,12 +215,15 @@ fcns_status fcns_autotune(fcns_ctx* ctx, char* report, int32_t report_len);
 
 /* Choose how rk_step runs the z pass of a stage (continuation, z
  * transforms, RK combine, projection and the back transforms of the new
- * state): on = 1 one fused kernel per stage (V* and the new state pass
- * through the caches within one workgroup), 0 three kernels (the default;
- * fcns_autotune picks the faster).  The fused form applies to FP64 contexts
- * with N' <= 288 and to stages whose output buffer is not their input (both
- * stages of o = 2); other stages keep three kernels.  EINVAL if on = 1 for a
- * context it does not apply to.  Results agree to rounding. */
+ * state): on = 1 one fused kernel per stage (V* and the new state stay in
+ * registers or pass through the caches within one workgroup), 0 three
+ * kernels; fcns_autotune picks the faster.  Until it is chosen, contexts of
+ * N' = 32 K run fused (the form with a wavefront per two pencils), others
+ * three kernels.  The fused form applies to FP64 contexts with N' <= 288 and
+ * to stages whose output buffer is not their input (both stages of o = 2, and
+ * for N' = 32 K every stage of o >= 2); other stages keep three kernels.
+ * EINVAL if on = 1 for a context it does not apply to.  Results agree to
+ * rounding. */
 fcns_status fcns_set_z_fused(fcns_ctx* ctx, int32_t on);
 
 /* Choose how rk_step runs the y and x passes of a stage (Sec. 4.2: the y

@@ -305,6 +305,11 @@ static XArgs xargs(const fcns_ctx* c, bool f32 = false) {
   return a;
 }
 
+// The fused z pass exists for this context / as one wavefront per two pencils
+// (z kernels of zwave.hip), which also takes stages whose output is their input.
+static bool can_fuse(const fcns_ctx* c) { return !c->mixed && z_pass_fits(zargs(c)); }
+static bool wave_z(const fcns_ctx* c) { return !c->mixed && z_wave_fits(zargs(c)); }
+
 // ---------------------------------------------------------------- create
 extern "C" fcns_status fcns_create(const fcns_problem* prob, void* hip_stream, fcns_ctx** out) {
   if (!out) return fail(nullptr, FCNS_EINVAL, "out is NULL");
@@ -431,6 +436,7 @@ extern "C" fcns_status fcns_create(const fcns_problem* prob, void* hip_stream, f
     delete c;
     return st;
   }
+  c->zfuse = wave_z(c);
   launch_fill(c->GW, 4 * g.npen, c->stream);
   *(volatile int*)c->hflag = 0;
   launch_fill(reinterpret_cast<cpx<double>*>(c->dflag), 1, c->stream);
@@ -711,7 +717,10 @@ static void z_part(fcns_ctx* c, cpx<double>* W, cpx<double>* OUT, double cj, boo
     ZArgs za = zargs(c);
     za.nonfinite = c->dflag;
     tbeg(c, T_ZPASS);
-    launch_z_pass(za, c->big_z, A, B, Z, nf, c->stream);
+    if (z_wave_fits(za))
+      launch_zw_pass(za, A, B, Z, nf, c->stream);
+    else
+      launch_z_pass(za, c->big_z, A, B, Z, nf, c->stream);
     tend(c);
     return;
   }
@@ -730,7 +739,20 @@ static void z_part(fcns_ctx* c, cpx<double>* W, cpx<double>* OUT, double cj, boo
   tend(c);
 }
 
-static bool can_fuse(const fcns_ctx* c) { return !c->mixed && z_pass_fits(zargs(c)); }
+
+// Input and output state of stage j of o.  fused: the stage runs a fused z
+// pass, which writes another buffer than it reads; the middle stages of o >= 3
+// then alternate between Q and VS (the scratch of the separate kernels) where
+// all stages do (the wavefront pass), and run the separate kernels in place
+// otherwise.
+static bool stage_buffers(const fcns_ctx* c, int j, int o, bool fuse, cpx<double>** W,
+                          cpx<double>** OUT) {
+  const bool wave = fuse && o > 1 && wave_z(c);
+  auto out = [&](int k) { return k == o ? c->P : wave && k % 2 == 0 ? c->VS : c->Q; };
+  *W = (j == 1) ? c->P : out(j - 1);
+  *OUT = out(j);
+  return fuse && *OUT != *W && can_fuse(c);
+}
 
 // One RK stage j of o (Sec. 4.4), c = dt/(o-j+1).  T: type of the transforms
 // and arrays of the nonlinear term (float in a mixed-precision context); the
@@ -739,11 +761,10 @@ static bool can_fuse(const fcns_ctx* c) { return !c->mixed && z_pass_fits(zargs(
 template <typename T>
 static void rk_stage(fcns_ctx* c, int j, int o, double dt) {
   const double cj = dt / (double)(o - j + 1);
-  cpx<double>* W = (j == 1) ? c->P : c->Q;
-  cpx<double>* OUT = (j == o) ? c->P : c->Q;
+  cpx<double>*W, *OUT;
+  const bool fused = stage_buffers(c, j, o, c->zfuse, &W, &OUT);
   // y-back, x-pass with products, y-fwd: nonlinear term in mixed space
   nonlinear_from_mixed<T>(c, reinterpret_cast<const cpx<T>*>(c->MV), c->nf, true);
-  const bool fused = c->zfuse && OUT != W && can_fuse(c);
   z_part<T>(c, W, OUT, cj, c->prob.keep_pressure && j == o, fused);
 }
 
@@ -1283,50 +1304,58 @@ struct fcns_batch {
   hipStream_t stream = nullptr;
   hipEvent_t ev_z = nullptr;
   std::vector<hipEvent_t> ev_ctx;
-  ZPassDesc* desc = nullptr;      // [o][n] on the device
+  ZPassDesc* desc = nullptr;      // [o][n] on the device, bucket by bucket
   std::vector<ZPassDesc> hdesc;   // the host copy they were made from
   std::vector<double> dt;         // per context
-  std::vector<double> cj;         // [o][n]
-  std::vector<char> fusable;      // per stage: the output buffer is not the input
-  long long groups = 0;
-  int max_npr = 0;
-  bool big = false;
-  size_t lds = 0;
+  // One launch per bucket and stage: the members of one N' = 32 K (npr), and
+  // those of any other length (npr = 0, the run-time plan engine).
+  struct Bucket {
+    int npr = 0, first = 0, n = 0;
+    long long groups = 0;
+    int max_npr = 0;
+    bool big = false;
+    size_t lds = 0;
+  };
+  std::vector<Bucket> buckets;
 };
 
 // The descriptors of every (stage, context) from the contexts as they are
-// now (their tables, parameters and buffers), and the launch shape.
+// now (their tables, parameters and buffers), and the launch shapes.
 static void batch_descriptors(fcns_batch* b, std::vector<ZPassDesc>& h) {
   const int n = (int)b->ctx.size(), o = b->o;
   h.resize((size_t)o * n);
   memset(h.data(), 0, h.size() * sizeof(ZPassDesc));
-  b->cj.assign((size_t)o * n, 0.0);
-  b->fusable.assign(o, 0);
-  b->max_npr = 0;
-  b->big = false;
-  b->lds = 0;
-  for (int j = 1; j <= o; ++j) {
-    long long wg = 0;
-    for (int i = 0; i < n; ++i) {
-      fcns_ctx* c = b->ctx[i];
-      cpx<double>* W = (j == 1) ? c->P : c->Q;
-      cpx<double>* OUT = (j == o) ? c->P : c->Q;
-      b->fusable[j - 1] = OUT != W;
-      const double cj = b->dt[i] / (double)(o - j + 1);
-      b->cj[(size_t)(j - 1) * n + i] = cj;
-      ZPassDesc& d = h[(size_t)(j - 1) * n + i];
+  auto key = [&](int i) { return wave_z(b->ctx[i]) ? b->ctx[i]->g.npr : 0; };
+  std::vector<int> order(n);
+  for (int i = 0; i < n; ++i) order[i] = i;
+  std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return key(x) < key(y); });
+  b->buckets.clear();
+  for (int s = 0; s < n; ++s) {
+    fcns_ctx* c = b->ctx[order[s]];
+    if (s == 0 || key(order[s]) != b->buckets.back().npr) {
+      b->buckets.emplace_back();
+      b->buckets.back().npr = key(order[s]);
+      b->buckets.back().first = s;
+    }
+    auto& bk = b->buckets.back();
+    for (int j = 1; j <= o; ++j) {
+      cpx<double>*W, *OUT;
+      stage_buffers(c, j, o, true, &W, &OUT);
+      const double cj = b->dt[order[s]] / (double)(o - j + 1);
+      ZPassDesc& d = h[(size_t)(j - 1) * n + s];
       d.a = zargs(c);
       d.a.nonfinite = c->dflag;
       z_part_args<double>(c, W, OUT, cj, c->prob.keep_pressure && j == o, true, d.sa, d.sb);
       d.zb = ZBackArgs{c->MV, c->M};
       d.nf = c->nf;
-      d.wg0 = wg;
-      wg += z_pass_groups(d.a);
-      b->max_npr = std::max(b->max_npr, c->g.npr);
-      b->big = b->big || c->big_z;
-      b->lds = std::max(b->lds, z_pass_lds(d.a));
+      d.wg0 = bk.groups;
     }
-    b->groups = wg;
+    const ZArgs a = zargs(c);
+    bk.n++;
+    bk.groups += z_pass_groups(a);
+    bk.max_npr = std::max(bk.max_npr, c->g.npr);
+    bk.big = bk.big || c->big_z;
+    bk.lds = std::max(bk.lds, z_pass_lds(a));
   }
 }
 
@@ -1403,24 +1432,36 @@ extern "C" fcns_status fcns_batch_run(fcns_batch* b, int32_t nsteps) {
   }
   for (int k = 0; k < nsteps; ++k)
     for (int j = 1; j <= o; ++j) {
+      bool any = false;
       for (int i = 0; i < n; ++i) {
         fcns_ctx* c = b->ctx[i];
         nonlinear_from_mixed<double>(c, c->MV, c->nf, true);
-        if (b->fusable[j - 1]) {
+        cpx<double>*W, *OUT;
+        if (stage_buffers(c, j, o, true, &W, &OUT)) {
+          any = true;
           (void)hipEventRecord(b->ev_ctx[i], c->stream);
           (void)hipStreamWaitEvent(b->stream, b->ev_ctx[i], 0);
         } else {
-          cpx<double>* W = (j == 1) ? c->P : c->Q;
-          cpx<double>* OUT = (j == o) ? c->P : c->Q;
-          z_part<double>(c, W, OUT, b->cj[(size_t)(j - 1) * n + i],
+          z_part<double>(c, W, OUT, b->dt[i] / (double)(o - j + 1),
                          c->prob.keep_pressure && j == o, false);
         }
       }
-      if (b->fusable[j - 1]) {
-        launch_z_pass_batch(b->desc + (size_t)(j - 1) * n, n, b->groups, b->max_npr, b->big,
-                            b->lds, b->stream);
-        (void)hipEventRecord(b->ev_z, b->stream);
-        for (fcns_ctx* c : b->ctx) (void)hipStreamWaitEvent(c->stream, b->ev_z, 0);
+      if (!any) continue;
+      for (const auto& bk : b->buckets) {
+        // (a bucket's members take the fused pass at the same stages: all but the
+        // only one of o = 1, and without the wavefront pass the middle ones of o >= 3)
+        if (o == 1 || (!bk.npr && j > 1 && j < o)) continue;
+        const ZPassDesc* d = b->desc + (size_t)(j - 1) * n + bk.first;
+        if (bk.npr)
+          launch_zw_pass_batch(d, bk.n, bk.groups, bk.npr, b->stream);
+        else
+          launch_z_pass_batch(d, bk.n, bk.groups, bk.max_npr, bk.big, bk.lds, b->stream);
+      }
+      (void)hipEventRecord(b->ev_z, b->stream);
+      for (int i = 0; i < n; ++i) {
+        cpx<double>*W, *OUT;
+        if (stage_buffers(b->ctx[i], j, o, true, &W, &OUT))
+          (void)hipStreamWaitEvent(b->ctx[i]->stream, b->ev_z, 0);
       }
     }
   fcns_status worst = FCNS_OK;

@@ -131,7 +131,17 @@ bool z_pass_fits(const ZArgs& a);
 void launch_z_pass(const ZArgs& a, bool big, const StageAArgs& sa, const StageBArgs& sb,
                    const ZBackArgs& zb, int nfields, hipStream_t st);
 
-// fc_derivative of contiguous lines, N' = 32 K (zwave.hip)
+// The same for N' = 32 K (zwave.hip), one wavefront per two pencils.
+bool z_wave_fits(const ZArgs& a);
+void launch_zw_pass(const ZArgs& a, const StageAArgs& sa, const StageBArgs& sb,
+                    const ZBackArgs& zb, int nfields, hipStream_t st);
+
+// the transforms alone, and fc_derivative of contiguous lines, in the same form
+void launch_zw_fwd(const ZArgs& a, const cpx<double>* src, cpx<double>* dst, long long sfs,
+                   long long dfs, int nfields, int filter, hipStream_t st);
+template <typename T>
+void launch_zw_back(const ZArgs& a, const cpx<double>* src, cpx<T>* dst, cpx<T>* dzdst,
+                    long long sfs, long long mfs, int nfields, hipStream_t st);
 bool zw_deriv_fits(const ZArgs& a, long long ps);
 void launch_zw_deriv(const ZArgs& a, const double* in, double* out, long long nlines,
                      long long ls, int order, hipStream_t st);
@@ -153,6 +163,8 @@ size_t z_pass_lds(const ZArgs& a);
 long long z_pass_groups(const ZArgs& a);
 void launch_z_pass_batch(const ZPassDesc* d, int n, long long groups, int max_npr, bool big,
                          size_t lds, hipStream_t st);
+// the same over problems of one N' = 32 K (z_wave_fits)
+void launch_zw_pass_batch(const ZPassDesc* d, int n, long long groups, int npr, hipStream_t st);
 void launch_fc_extend(const double* in, long long nlines, long long ips, long long ils, double* out,
                       long long ops, long long ols, int nz, int C, int d, const double* M,
                       hipStream_t st);

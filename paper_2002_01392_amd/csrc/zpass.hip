@@ -1016,6 +1016,10 @@ static bool z_static_282(const ZArgs& a) { return a.g.npr == 282 && plan_is(a.pl
 
 void launch_z_fwd(const ZArgs& a, bool big, const cpx<double>* src, cpx<double>* dst,
                   long long sfs, long long dfs, int nfields, int filter, hipStream_t st) {
+  if (z_wave_fits(a)) {
+    launch_zw_fwd(a, src, dst, sfs, dfs, nfields, filter, st);
+    return;
+  }
   dim3 grid((unsigned)((a.g.npen + ZPB - 1) / ZPB), nfields);
   const size_t sh = zshared_bytes<double>(a.g, a.pl.tsize);
   if (z_static_288(a))
@@ -1034,6 +1038,10 @@ void launch_z_fwd(const ZArgs& a, bool big, const cpx<double>* src, cpx<double>*
 template <typename T>
 void launch_z_back(const ZArgs& a, bool big, const cpx<double>* src, cpx<T>* dst, cpx<T>* dzdst,
                    long long sfs, long long mfs, int nfields, hipStream_t st) {
+  if (z_wave_fits(a)) {
+    launch_zw_back<T>(a, src, dst, dzdst, sfs, mfs, nfields, st);
+    return;
+  }
   dim3 grid((unsigned)((a.g.npen + ZPB - 1) / ZPB), nfields);
   const size_t sh = zshared_bytes<T>(a.g, a.pl.tsize);
   const int own = pick_own(a.g.npr);
@@ -1126,32 +1134,11 @@ void launch_z_pass(const ZArgs& a, bool big, const StageAArgs& sa, const StageBA
   dim3 grid((unsigned)((a.g.npen + ZPB - 1) / ZPB));
   const size_t sh = zshared_bytes<double>(a.g, a.pl.tsize);
   const int own = pick_own(a.g.npr);
+  // (N' = 32 K with the stored tables runs launch_zw_pass instead)
   if (z_static_288(a)) {
-    bool wv = true;  // W is V^t for every field (the first RK stage)
-    for (int f = 0; f < nfields; ++f) wv = wv && sa.w[f] == sa.vt[f];
-    if (wv)
-      FCNS_LAUNCH((k_z_pass<P288, 9, true>), grid, dim3(ZNT), sh, st, a, sa, sb, zb, nfields);
-    else
-      FCNS_LAUNCH((k_z_pass<P288, 9, false>), grid, dim3(ZNT), sh, st, a, sa, sb, zb, nfields);
+    FCNS_LAUNCH((k_z_pass<P288, 9, false>), grid, dim3(ZNT), sh, st, a, sa, sb, zb, nfields);
   } else if (z_static_282(a)) {
     FCNS_LAUNCH((k_z_pass<P282, 9, false>), grid, dim3(ZNT), sh, st, a, sa, sb, zb, nfields);
-  } else if (own == 9 && plan_is(a.pl, {8, 4, 7})) {
-    // N' = 224, 160, 128, 96 and 64 (the sides 192, 128, 96, 64 and 32 with
-    // C = 31): compiled plans, N' / 32 rows per thread
-    FCNS_LAUNCH((k_z_pass<SPlan<8, 4, 7>, 7, false>), grid, dim3(ZNT), sh, st, a, sa, sb, zb,
-                nfields);
-  } else if (own == 9 && plan_is(a.pl, {8, 4, 5})) {
-    FCNS_LAUNCH((k_z_pass<SPlan<8, 4, 5>, 5, false>), grid, dim3(ZNT), sh, st, a, sa, sb, zb,
-                nfields);
-  } else if (own == 4 && plan_is(a.pl, {8, 8, 2})) {
-    FCNS_LAUNCH((k_z_pass<SPlan<8, 8, 2>, 4, false>), grid, dim3(ZNT), sh, st, a, sa, sb, zb,
-                nfields);
-  } else if (own == 4 && plan_is(a.pl, {8, 4, 3})) {
-    FCNS_LAUNCH((k_z_pass<SPlan<8, 4, 3>, 3, false>), grid, dim3(ZNT), sh, st, a, sa, sb, zb,
-                nfields);
-  } else if (own == 4 && plan_is(a.pl, {8, 8})) {
-    FCNS_LAUNCH((k_z_pass<SPlan<8, 8>, 2, false>), grid, dim3(ZNT), sh, st, a, sa, sb, zb,
-                nfields);
   } else if (big) {
     if (own <= 4)
       FCNS_LAUNCH((k_z_pass<DynPlan<true>, 4, false>), grid, dim3(ZNT), sh, st, a, sa, sb, zb,
