@@ -1094,10 +1094,12 @@ extern "C" fcns_status fcns_autotune(fcns_ctx* c, char* report, int32_t report_l
   // state (a compiled plan, when the length has one, is kept)
   {
     std::vector<int> rs = z_radices(g.npr);
+    // (the wavefront kernels of N' = 32 K use no plan)
     const bool compiled = g.npr == 288 && rs == std::vector<int>{16, 18};
+    const bool planless = z_wave_fits(zargs(c));
     std::vector<int> best_rs = rs;
     float best = 1e30f;
-    if (!compiled) {
+    if (!compiled && !planless) {
       std::vector<int> perm = rs;
       std::sort(perm.begin(), perm.end());
       int n = 0;
@@ -1124,8 +1126,8 @@ extern "C" fcns_status fcns_autotune(fcns_ctx* c, char* report, int32_t report_l
     }
     rep += "z: radices";
     for (int r : best_rs) rep += " " + std::to_string(r);
-    if (compiled) {
-      rep += " (compiled plan)";
+    if (compiled || planless) {
+      rep += planless ? " (wavefront kernels)" : " (compiled plan)";
     } else {
       snprintf(line, sizeof(line), " (%.3f ms)", best);
       rep += line;

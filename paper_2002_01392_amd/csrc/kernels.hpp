@@ -15,9 +15,13 @@ constexpr int ZLS = ZNT / ZPB;  // rows a thread steps over (its pencil is tid %
 constexpr int YL = 4;
 constexpr int YNT = 256;
 constexpr long long Y_GRID = 1024;  // persistent y workgroups per field
-// x kernels: XR rows per workgroup (XR/2 complex lines); nx <= XNT
-constexpr int XR = 8;
-constexpr int XNT = 512;
+// x kernels: LDS line stride of the tiled ones (4 mod 8 slots, so the lines
+// interleaved by the thread mapping fall on different banks), and the row
+// lengths that wavefronts transform on their own (xwave.hpp)
+__host__ __device__ inline int x_ls(int nx) { return ((nx + nx / 8 + 7) / 8) * 8 + 4; }
+inline bool x_wave_rows(int nx) {
+  return nx == 512 || nx == 256 || nx == 192 || nx == 128 || nx == 96 || nx == 64 || nx == 32;
+}
 
 // Does the run-time plan have exactly these radices (in this order)?
 inline bool plan_is(const FFTPlan& pl, std::initializer_list<int> rs) {
@@ -78,7 +82,7 @@ bool y_wide_tiles(const YArgs& a);
 struct XArgs {
   int nx, nkx, nkxp, ny;
   double kxs;
-  FFTPlan pl;        // nx-point plan (lines = XR/2, threads = XNT)
+  FFTPlan pl;        // nx-point plan
   const void* tw;    // nx twiddles
   int variant;       // x pass with products: 0 default, 1 tiled 4 rows x 256, 2 tiled 8 x 512,
                      // 3 tiled 8 rows x nx threads (nx <= 256)

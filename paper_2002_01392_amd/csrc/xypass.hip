@@ -7,6 +7,7 @@
 // transforms use IFFT(y) = conj(FFT(conj(y))) / n with the conjugations folded
 // into loads and stores.
 #include "kernels.hpp"
+#include "xwave.hpp"
 
 #include <type_traits>
 
@@ -32,12 +33,12 @@ bool y_wide_tiles(const YArgs& a) { return a.ny == 512 && plan_is(a.pl, {8, 8, 8
 
 // PF: load the next tile into registers while the current one is transformed
 // (more registers, fewer waves per SIMD) or load each tile when it is needed.
-// LT lines per tile, 64 LT threads (64 rows stepped per thread either way).
-template <typename T, class FP, int OWN, bool PF, int LT>
-__global__ __launch_bounds__(64 * LT) void k_y(YArgs a, const cpx<T>* src, cpx<T>* dst,
+// LT lines per tile, NT threads.
+template <typename T, class FP, int OWN, bool PF, int LT, int NT>
+__global__ __launch_bounds__(NT) void k_y(YArgs a, const cpx<T>* src, cpx<T>* dst,
                                                cpx<T>* dst2, long long sfs, long long dfs,
                                                long long nlines, int inv, int mode) {
-  constexpr int YL = LT, YNT = 64 * LT;
+  constexpr int YL = LT, YNT = NT;
   extern __shared__ __align__(16) char smem[];
   const int tid = threadIdx.x;
   const int ny = FP::dynamic ? a.ny : FP::n;
@@ -179,124 +180,10 @@ __global__ __launch_bounds__(64 * LT) void k_y(YArgs a, const cpx<T>* src, cpx<T
 }
 
 // ---------------------------------------------------------------- x helpers
-// Rows r0..r0+XR-1; two real rows (2a, 2a+1) share complex line a:
-// z[n] = x_2a[n] + i x_2a+1[n], staged in LDS line-contiguous with the padded
-// layout of the FFT engine, element n of line a at xp(a, n) (line stride
-// x_ls(nx) = 4 mod 8 slots, so the lines interleaved by the thread mapping
-// fall on different banks).
-constexpr int XL = XR / 2;
-
-__host__ __device__ inline int x_ls(int nx) { return ((nx + nx / 8 + 7) / 8) * 8 + 4; }
+// Two real rows share one complex line, staged in LDS line-contiguous with the
+// padded layout of the FFT engine, element n of line a at xp(a, n) (x_ls:
+// line stride).
 __device__ __forceinline__ int xp(int a, int n, int ls) { return lds_pos<true>(a, n, 1, ls); }
-
-// Pack the spectra A (row 2a), B (row 2a+1) of two real rows into the
-// conjugate of the full spectrum of z = x_2a + i x_2a+1 (ready for the inverse
-// via the conjugated forward transform).  The imaginary parts of the kx = 0
-// and kx = nx/2 bins are dropped, as a c2r transform does.  dx: multiply by
-// i k~x first.
-template <typename T>
-__device__ __forceinline__ void x_pack_c2r(cpx<T>* X, int ls, const cpx<double>* __restrict__ xy,
-                                           long long r0, long long nrows, const XArgs& a,
-                                           bool dx, int tid) {
-  const int nx = a.nx, nkx = a.nkx, nkxp = a.nkxp;
-#pragma unroll
-  for (int al = 0; al < XL; ++al) {
-    const long long ra = r0 + 2 * al, rb = ra + 1;
-    for (int k = tid; k < nkx; k += XNT) {
-      cpx<double> A = (ra < nrows) ? xy[ra * nkxp + k] : zero<double>();
-      cpx<double> B = (rb < nrows) ? xy[rb * nkxp + k] : zero<double>();
-      if (dx) {
-        const double kx = (2 * k == nx) ? 0.0 : a.kxs * k;
-        A = mul_i(A) * kx;
-        B = mul_i(B) * kx;
-      }
-      if (k == 0 || 2 * k == nx) {
-        A.y = 0.0;
-        B.y = 0.0;
-      }
-      // Z[k] = A + i B, Z[nx - k] = conj(A) + i conj(B); store conjugates
-      X[xp(al, k, ls)] = cvt<T>(conj(mk(A.x - B.y, A.y + B.x)));
-      if (k > 0 && 2 * k < nx) X[xp(al, nx - k, ls)] = cvt<T>(conj(mk(A.x + B.y, B.x - A.y)));
-    }
-  }
-}
-
-// Unpack the forward transform of two packed real rows into their r2c spectra.
-template <typename T>
-__device__ __forceinline__ void x_unpack_r2c(const cpx<T>* X, int ls, cpx<double>* __restrict__ xy,
-                                             long long r0, long long nrows, const XArgs& a,
-                                             int tid) {
-  const int nx = a.nx, nkx = a.nkx, nkxp = a.nkxp;
-#pragma unroll
-  for (int al = 0; al < XL; ++al) {
-    const long long ra = r0 + 2 * al, rb = ra + 1;
-    for (int k = tid; k < nkx; k += XNT) {
-      const cpx<double> Z = cvt<double>(X[xp(al, k, ls)]);
-      const cpx<double> Zm = conj(cvt<double>(X[xp(al, ((k == 0) ? 0 : nx - k), ls)]));
-      if (ra < nrows) xy[ra * nkxp + k] = (Z + Zm) * 0.5;
-      if (rb < nrows) xy[rb * nkxp + k] = mul_mi(Z - Zm) * 0.5;
-    }
-  }
-}
-
-// ---------------------------------------------------------------- x r2c / c2r
-template <typename T, bool BIG>
-__global__ __launch_bounds__(XNT) void k_x_r2c(XArgs a, const double* __restrict__ phys,
-                                               cpx<double>* __restrict__ xy, long long pfs,
-                                               long long xfs, long long nrows) {
-  extern __shared__ __align__(16) char smem[];
-  const int tid = threadIdx.x;
-  const int nx = a.nx, ls = x_ls(nx);
-  cpx<T>* tw = reinterpret_cast<cpx<T>*>(smem);
-  cpx<T>* X0 = tw + a.pl.tsize;
-  cpx<T>* X1 = X0 + XL * ls;
-  phys += blockIdx.y * pfs;
-  xy += blockIdx.y * xfs;
-  const cpx<T>* gtw = reinterpret_cast<const cpx<T>*>(a.tw);
-  for (int i = tid; i < a.pl.tsize; i += XNT) tw[i] = gtw[i];
-  const long long r0 = (long long)blockIdx.x * XR;
-  T* Xs = reinterpret_cast<T*>(X0);
-#pragma unroll
-  for (int rl = 0; rl < XR; ++rl) {
-    const long long r = r0 + rl;
-    for (int n = tid; n < nx; n += XNT)
-      Xs[2 * xp(rl >> 1, n, ls) + (rl & 1)] = (r < nrows) ? (T)phys[r * nx + n] : T(0);
-  }
-  __syncthreads();
-  const cpx<T>* R = fft_fwd<T, XL, BIG, true>(X0, X1, 1, ls, a.pl, tw, tid, XNT);
-  x_unpack_r2c<T>(R, ls, xy, r0, nrows, a, tid);
-}
-
-template <typename T, bool BIG>
-__global__ __launch_bounds__(XNT) void k_x_c2r(XArgs a, const cpx<double>* __restrict__ xy,
-                                               double* __restrict__ phys, long long xfs,
-                                               long long pfs, long long nrows) {
-  extern __shared__ __align__(16) char smem[];
-  const int tid = threadIdx.x;
-  const int nx = a.nx, ls = x_ls(nx);
-  cpx<T>* tw = reinterpret_cast<cpx<T>*>(smem);
-  cpx<T>* X0 = tw + a.pl.tsize;
-  cpx<T>* X1 = X0 + XL * ls;
-  phys += blockIdx.y * pfs;
-  xy += blockIdx.y * xfs;
-  const cpx<T>* gtw = reinterpret_cast<const cpx<T>*>(a.tw);
-  for (int i = tid; i < a.pl.tsize; i += XNT) tw[i] = gtw[i];
-  const long long r0 = (long long)blockIdx.x * XR;
-  x_pack_c2r<T>(X0, ls, xy, r0, nrows, a, false, tid);
-  __syncthreads();
-  const cpx<T>* R = fft_fwd<T, XL, BIG, true>(X0, X1, 1, ls, a.pl, tw, tid, XNT);
-  const double sc = 1.0 / nx;
-#pragma unroll
-  for (int al = 0; al < XL; ++al) {
-    const long long ra = r0 + 2 * al, rb = ra + 1;
-    for (int n = tid; n < nx; n += XNT) {
-      // z = conj(R) / nx: row 2a = Re z, row 2a+1 = Im z
-      const cpx<T> z = R[xp(al, n, ls)];
-      if (ra < nrows) phys[ra * nx + n] = (double)z.x * sc;
-      if (rb < nrows) phys[rb * nx + n] = -(double)z.y * sc;
-    }
-  }
-}
 
 // ---------------------------------------------------------------- x pass with products
 // NL_f = -(u dq_f/dx + v dq_f/dy + w dq_f/dz) at the physical points of RR
@@ -436,373 +323,159 @@ __global__ __launch_bounds__(NT) void k_x_nl(XArgs a, const cpx<T>* __restrict__
   }
 }
 
+// The same for run-time plans of short rows: 8 rows per workgroup, and three
+// quantities (u, v, w; dq/dx, dq/dy, dq/dz of a field) transformed together as 12
+// complex lines, so that a radix stage of 12 nx / R butterflies fills the 256
+// threads (4 lines of 120 points leave three quarters idle) and the row tile
+// makes 2 + F rounds of transforms and barriers instead of 3 + 4 F.  The next
+// round's spectra are loaded during a round's transform.  A convection solve of
+// 120 x 84 x 81 with this kernel and 8-line y tiles: 18.6 -> 12.9 ms (x pass 0.21 ms
+// per stage before).
+constexpr int X3_NT = 256, X3_L = 12, X3_CE = 5, X3_CP = 3;
+constexpr int X3_MAXNX = 192;   // 12 nkxp <= X3_CE X3_NT, 4 nx <= X3_CP X3_NT
+template <typename T>
+static size_t x3_lds(const XArgs& a) {
+  return ((size_t)a.pl.tsize + 2 * X3_L * x_ls(a.nx)) * sizeof(cpx<T>);
+}
+
+// e / n for 0 <= e < 2^20 (rcp = 1 / n): the float quotient is off by at most one
+__device__ __forceinline__ int x3_div(int e, int n, float rcp) {
+  int q = (int)((float)e * rcp);
+  if (q * n > e) --q;
+  if (q * n + n <= e) ++q;
+  return q;
+}
+
+template <typename T, int NF, bool BIG>
+__global__ __launch_bounds__(X3_NT) void k_x_nl3(XArgs a, const cpx<T>* __restrict__ xyb,
+                                                 cpx<T>* __restrict__ nl, long long fs,
+                                                 long long nrows) {
+  extern __shared__ __align__(16) char smem[];
+  const int tid = threadIdx.x;
+  const int nx = a.nx, nkx = a.nkx, nkxp = a.nkxp, ls = x_ls(nx);
+  cpx<T>* tw = reinterpret_cast<cpx<T>*>(smem);
+  cpx<T>* X0 = tw + a.pl.tsize;
+  cpx<T>* X1 = X0 + X3_L * ls;
+  const cpx<T>* gtw = reinterpret_cast<const cpx<T>*>(a.tw);
+  for (int i = tid; i < a.pl.tsize; i += X3_NT) tw[i] = gtw[i];
+  const long long r0 = (long long)blockIdx.x * 8;
+  const T sc = T(1) / (T)nx;
+  const float rnk = 1.0f / (float)nkxp, rnx = 1.0f / (float)nx;
+  // this thread's spectral elements: column ek of line el (quantity el / 4, row
+  // pair el % 4) at e = tid + c X3_NT of the 12 nkxp; -1: none
+  int el[X3_CE], ek[X3_CE];
+#pragma unroll
+  for (int c = 0; c < X3_CE; ++c) {
+    const int e = tid + c * X3_NT;
+    el[c] = x3_div(e, nkxp, rnk);
+    ek[c] = e - el[c] * nkxp;
+    if (el[c] >= X3_L || ek[c] >= nkx) el[c] = -1;
+  }
+  // and physical points: column pn of row pair pa; -1: none
+  int pa[X3_CP], pn[X3_CP];
+#pragma unroll
+  for (int c = 0; c < X3_CP; ++c) {
+    const int e = tid + c * X3_NT;
+    pa[c] = x3_div(e, nx, rnx);
+    pn[c] = e - pa[c] * nx;
+    if (pa[c] >= 4) pa[c] = -1;
+  }
+  cpx<T> in[X3_CE][2];
+  // round 0: u, v, w; round 1 + f: the derivatives of field f
+  auto load = [&](int round) {
+#pragma unroll
+    for (int c = 0; c < X3_CE; ++c) {
+      const int q = el[c] >> 2, al = el[c] & 3;
+      const int slot = round == 0 ? 3 * q : 3 * (round - 1) + q;
+      const long long ra = r0 + 2 * al;
+      const cpx<T>* src = xyb + slot * fs + ra * nkxp + ek[c];
+      in[c][0] = (el[c] >= 0 && ra < nrows) ? src[0] : zero<T>();
+      in[c][1] = (el[c] >= 0 && ra + 1 < nrows) ? src[nkxp] : zero<T>();
+    }
+  };
+  T U[3][X3_CP][2], acc[NF][X3_CP][2];
+  load(0);
+#pragma unroll
+  for (int round = 0; round <= NF; ++round) {
+#pragma unroll
+    for (int c = 0; c < X3_CE; ++c) {
+      if (el[c] < 0) continue;
+      const int k = ek[c];
+      cpx<T> A = in[c][0], B = in[c][1];
+      if (round > 0 && el[c] < 4) {
+        const T kx = (2 * k == nx) ? T(0) : (T)(a.kxs * k);
+        A = mul_i(A) * kx;
+        B = mul_i(B) * kx;
+      }
+      if (k == 0 || 2 * k == nx) A.y = B.y = T(0);
+      // Z[k] = A + i B, Z[nx - k] = conj(A) + i conj(B); stored conjugated
+      X0[lds_pos<true>(el[c], k, 1, ls)] = conj(mk(A.x - B.y, A.y + B.x));
+      if (k > 0 && 2 * k < nx)
+        X0[lds_pos<true>(el[c], nx - k, 1, ls)] = conj(mk(A.x + B.y, B.x - A.y));
+    }
+    if (round < NF) load(round + 1);
+    __syncthreads();
+    const cpx<T>* R = fft_fwd<T, X3_L, BIG, true>(X0, X1, 1, ls, a.pl, tw, tid, X3_NT);
+#pragma unroll
+    for (int c = 0; c < X3_CP; ++c) {
+      if (pa[c] < 0) continue;
+      T v[3][2];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        const cpx<T> z = R[lds_pos<true>(4 * d + pa[c], pn[c], 1, ls)];
+        v[d][0] = z.x * sc;
+        v[d][1] = -z.y * sc;
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if (round == 0) {
+          U[0][c][h] = v[0][h];
+          U[1][c][h] = v[1][h];
+          U[2][c][h] = v[2][h];
+        } else {
+          T s = -U[0][c][h] * v[0][h];
+          s -= U[1][c][h] * v[1][h];
+          s -= U[2][c][h] * v[2][h];
+          acc[round > 0 ? round - 1 : 0][c][h] = s;
+        }
+      }
+    }
+    __syncthreads();
+  }
+  // forward transforms: fields 0..2 together, then theta
+  auto forward = [&](auto lc, int f0) {
+    constexpr int L = decltype(lc)::value;
+#pragma unroll
+    for (int c = 0; c < X3_CP; ++c) {
+      if (pa[c] < 0) continue;
+#pragma unroll
+      for (int f = 0; f < L / 4; ++f)
+        X0[lds_pos<true>(4 * f + pa[c], pn[c], 1, ls)] =
+            mk(acc[(L == 4 ? NF - 1 : f)][c][0], acc[(L == 4 ? NF - 1 : f)][c][1]);
+    }
+    __syncthreads();
+    const cpx<T>* R = fft_fwd<T, L, BIG, true>(X0, X1, 1, ls, a.pl, tw, tid, X3_NT);
+#pragma unroll
+    for (int c = 0; c < X3_CE; ++c) {
+      if (el[c] < 0 || el[c] >= L) continue;
+      const int k = ek[c], al = el[c] & 3;
+      const cpx<T> Z = R[lds_pos<true>(el[c], k, 1, ls)];
+      const cpx<T> Zm = conj(R[lds_pos<true>(el[c], k == 0 ? 0 : nx - k, 1, ls)]);
+      const long long ra = r0 + 2 * al;
+      cpx<T>* dst = nl + (f0 + (el[c] >> 2)) * fs + ra * nkxp + k;
+      if (ra < nrows) dst[0] = (Z + Zm) * T(0.5);
+      if (ra + 1 < nrows) dst[nkxp] = mul_mi(Z - Zm) * T(0.5);
+    }
+  };
+  forward(std::integral_constant<int, 12>{}, 0);
+  if constexpr (NF == 4) {
+    __syncthreads();
+    forward(std::integral_constant<int, 4>{}, 3);
+  }
+}
+
 // ---------------------------------------------------------------- x pass, wave-level rows
-// Rows of N = 512, 256, 192, 128, 96, 64 or 32 points with 8 points per
-// lane: a row occupies S = N / 8 lanes (one row per wavefront at 512, two at
-// 256 and 192, four at 128, five at 96, eight at 64, sixteen at 32), and
-// lane t of a row (t < S) holds index t + S m (m = 0..7) of every
-// transform, in and out.
-//
-// N = 512 = 8 x 8 x 8: n = n0 + 8 n1 + 64 n2, k = k0 + 8 k1 + 64 k2 (t = n0 + 8 n1):
-//   a radix-8 DFT over n2 in registers, twiddle w64^(n1 k0);
-//   exchange so that lane n0 + 8 k0 holds n1 = 0..7, radix-8 over n1,
-//   twiddle w512^(n0 (k0 + 8 k1));
-//   exchange so that lane k0 + 8 k1 holds n0 = 0..7, radix-8 over n0,
-// which leaves X[t + 64 k2] in lane t.
-// N = 256 = 8 x 32: n = t + 32 m, k = a + 8 b:
-//   a radix-8 DFT over m in registers, twiddle w256^(t a);
-//   the eight 32-point DFTs over t = t0 + 4 t1 (b = j1 + 8 j0): exchange so
-//   that lane t0 + 4 a holds t1 = 0..7, radix-8 over t1, twiddle w32^(t0 j1);
-//   exchange so that lane L holds t0 = 0..3 of c = a + 8 j1 = L and L + 32,
-//   two radix-4 DFTs over t0,
-// which leaves X[c + 64 j0] = X[L + 32 (h + 2 j0)] (c = L + 32 h) in lane L.
-// N = 128 = 8 x 16: n = t + 16 m, k = a + 8 b:
-//   a radix-8 DFT over m in registers, twiddle w128^(t a);
-//   the eight 16-point DFTs over t = h + 2 t1 (b = j + 8 c): exchange so that
-//   lane 2 a + h holds t1 = 0..7, radix-8 over t1, twiddle w16^(h j);
-//   exchange so that lane a + 8 j0 holds, for j = j0 + 2 j1 (j1 = 0..3),
-//   both halves h of output j, and a radix-2 DFT over h,
-// which leaves X[a + 8 j + 64 c] = X[L + 16 (j1 + 4 c)] in lane L.
-// N = 64 = 8 x 8: a radix-8 DFT over m, twiddle w64^(t a), one exchange so
-// that lane a holds t = 0..7, radix-8 over t: X[a + 8 b] in lane a.
-// N = 32 = 8 x 4: a radix-8 DFT over m, twiddle w32^(t a), one exchange so
-// that lane L holds t = 0..3 of a = 2L and 2L + 1, two radix-4 DFTs, and a
-// last exchange into natural order.
-// N = 192 = 8 x 24 and 96 = 8 x 12 (S = 24, 12 lanes; 2 and 5 rows per
-// wavefront, the 64 mod S spare lanes repeat a row's last lanes and store
-// nothing): a radix-8 DFT over m, twiddle wN^(t a); the S-point DFTs over
-// t = h + 3 t1 (b = j + (S/3) c): exchange so that a lane holds, for its
-// (a, h), t1 = 0..S/3-1 (at 96 two values of a per lane), radix-8 (192) or
-// two radix-4 (96) DFTs over t1, twiddle wS^(h j); exchange, radix-3 DFTs
-// over h (X[a + 8 j + (8 S/3) c], c = 0..2) spread over the lanes, and a
-// last exchange into natural order.
-// The exchanges go through a padded per-row LDS buffer (conflict-free
-// 16-byte accesses) and need only wave-level ordering, no workgroup barrier.
-// Two real transforms share one complex transform: z = a + i b (inverse from
-// the spectra A, B; forward of two nonlinear terms).
-constexpr int XW_WAVES = 4;        // waves per workgroup
-constexpr int XW_BUF = 512 + 64;   // padded slots of one wave's exchange buffer(s)
-
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Padded slots, written with the per-lane part separate so that the
-// per-register part is an instruction offset.  N = 512: element
-// 64 n0 + 8 k0 + n1 of exchange 1 sits at 65 n0 + 8 k0 + n1, element
-// 8 j + n0 of exchange 2 at 9 j + n0.  N = 256: element (a, t) of exchange 1
-// at 36 a + t, element (c, t0) of exchange 2 at 4 c + c / 4 + t0.  Both: element
-// i of the natural-order buffer at i + i / 8.
-__device__ __forceinline__ int xw_nat(int i) { return i + (i >> 3); }
-
-// Per-lane twiddles, stored [register][t] in LDS (read at t + offset).
-// N = 512: tw[k0 - 1][t] = w64^(n1 k0) (k0 = 1..7) with t = n0 + 8 n1, and
-// tw[7 + k1][t] = w512^(n0 (k0' + 8 k1)) with t = n0 + 8 k0'.
-// N = 256: tw[a - 1][t] = w256^(t a) (a = 1..7), tw[6 + j1][t] = w32^(t0 j1)
-// (j1 = 1..7) with t = t0 + 4 a.  N = 128: tw[a - 1][t] = w128^(t a),
-// tw[6 + j][L] = w16^(h j) with h = L & 1.  N = 64: tw[a - 1][t] = w64^(t a).
-// N = 192, 96: tw[a - 1][t] = wN^(t a), tw[6 + j][L] = w(N/8)^(h j) with
-// h = L mod 3.  N = 32: tw[a - 1][t] = w32^(t a).
-constexpr int XW_TW = 15 * 64;
-
-template <typename T, int N>
-__device__ __forceinline__ void xw_twiddles(cpx<T>* tw, int tid) {
-  constexpr int S = N / 8, NTW = (N == 512 ? 15 : 14) * S;
-  static_assert(NTW <= XW_TW, "twiddle table");
-  for (int e = tid; e < NTW; e += 64 * XW_WAVES) {
-    const int reg = e / S, t = e % S;
-    int j;  // power of wN
-    if (N == 512)
-      j = reg < 7 ? 8 * (t >> 3) * (reg + 1) : (t & 7) * ((t >> 3) + 8 * (reg - 7));
-    else if (N == 256)
-      j = reg < 7 ? t * (reg + 1) : 8 * (t & 3) * (reg - 6);
-    else if (N == 128)   // tw[6 + j][L] = w16^(h j), h = L & 1
-      j = reg < 7 ? t * (reg + 1) : 8 * (t & 1) * (reg - 6);
-    else if (N == 192 || N == 96)   // tw[6 + j][L] = w(N/8)^(h j), h = L mod 3
-      j = reg < 7 ? t * (reg + 1) : 8 * (t % 3) * (reg - 6);
-    else
-      j = reg < 7 ? t * (reg + 1) : 0;
-    double sn, cs;
-    sincospi(2.0 * j / N, &sn, &cs);
-    tw[e] = mk((T)cs, (T)(-sn));   // exp(-2 pi i j / N)
-  }
-}
-
-template <typename T>
-__device__ __forceinline__ void wave_fft512(cpx<T> (&r)[8], cpx<T>* __restrict__ buf,
-                                            const cpx<T>* __restrict__ tw, int lane) {
-  const int n0 = lane & 7, hi = lane >> 3;  // hi = n1 before, k0 after exchange 1
-  Codelet<T, 8>::run(r, nullptr);
-#pragma unroll
-  for (int k0 = 1; k0 < 8; ++k0) r[k0] = r[k0] * tw[(k0 - 1) * 64 + lane];
-  cpx<T>* w1 = buf + 65 * n0 + hi;
-#pragma unroll
-  for (int k0 = 0; k0 < 8; ++k0) w1[8 * k0] = r[k0];
-  wave_sync();
-  const cpx<T>* r1 = buf + 65 * n0 + 8 * hi;
-#pragma unroll
-  for (int n1 = 0; n1 < 8; ++n1) r[n1] = r1[n1];
-  wave_sync();
-  Codelet<T, 8>::run(r, nullptr);
-#pragma unroll
-  for (int k1 = 0; k1 < 8; ++k1) r[k1] = r[k1] * tw[(7 + k1) * 64 + lane];
-  cpx<T>* w2 = buf + 9 * hi + n0;
-#pragma unroll
-  for (int k1 = 0; k1 < 8; ++k1) w2[72 * k1] = r[k1];
-  wave_sync();
-  const cpx<T>* r2 = buf + 9 * lane;
-#pragma unroll
-  for (int q = 0; q < 8; ++q) r[q] = r2[q];
-  wave_sync();
-  Codelet<T, 8>::run(r, nullptr);
-}
-
-template <typename T>
-__device__ __forceinline__ void wave_fft256(cpx<T> (&r)[8], cpx<T>* __restrict__ buf,
-                                            const cpx<T>* __restrict__ tw, int t) {
-  Codelet<T, 8>::run(r, nullptr);
-#pragma unroll
-  for (int a = 1; a < 8; ++a) r[a] = r[a] * tw[(a - 1) * 32 + t];
-  cpx<T>* w1 = buf + t;
-#pragma unroll
-  for (int a = 0; a < 8; ++a) w1[36 * a] = r[a];
-  wave_sync();
-  const int t0 = t & 3, a = t >> 2;  // the lane's (t0, a) after exchange 1
-  const cpx<T>* r1 = buf + 36 * a + t0;
-#pragma unroll
-  for (int t1 = 0; t1 < 8; ++t1) r[t1] = r1[4 * t1];
-  wave_sync();
-  Codelet<T, 8>::run(r, nullptr);
-#pragma unroll
-  for (int j1 = 1; j1 < 8; ++j1) r[j1] = r[j1] * tw[(6 + j1) * 32 + t];
-  // c = a + 8 j1: 4 c + c / 4 + t0 = (4 a + a / 4 + t0) + 34 j1
-  cpx<T>* w2 = buf + 4 * a + (a >> 2) + t0;
-#pragma unroll
-  for (int j1 = 0; j1 < 8; ++j1) w2[34 * j1] = r[j1];
-  wave_sync();
-  // c = t + 32 h: 4 c + c / 4 = (4 t + t / 4) + 136 h
-  const cpx<T>* r2 = buf + 4 * t + (t >> 2);
-  cpx<T> q[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) q[i] = r2[136 * (i >> 2) + (i & 3)];
-  wave_sync();
-  dft4_reg<T>(q[0], q[1], q[2], q[3]);
-  dft4_reg<T>(q[4], q[5], q[6], q[7]);
-  // q[4 h + j0] = X[t + 32 (h + 2 j0)]
-#pragma unroll
-  for (int m = 0; m < 8; ++m) r[m] = q[4 * (m & 1) + (m >> 1)];
-}
-
-template <typename T>
-__device__ __forceinline__ void wave_fft128(cpx<T> (&r)[8], cpx<T>* __restrict__ buf,
-                                            const cpx<T>* __restrict__ tw, int t) {
-  Codelet<T, 8>::run(r, nullptr);
-#pragma unroll
-  for (int a = 1; a < 8; ++a) r[a] = r[a] * tw[(a - 1) * 16 + t];
-  // exchange 1: element (a, t) at 17 a + t
-  cpx<T>* w1 = buf + t;
-#pragma unroll
-  for (int a = 0; a < 8; ++a) w1[17 * a] = r[a];
-  wave_sync();
-  const int a = t >> 1, h = t & 1;  // the lane's (a, h) after exchange 1
-  const cpx<T>* r1 = buf + 17 * a + h;
-#pragma unroll
-  for (int t1 = 0; t1 < 8; ++t1) r[t1] = r1[2 * t1];
-  wave_sync();
-  Codelet<T, 8>::run(r, nullptr);
-#pragma unroll
-  for (int j = 1; j < 8; ++j) r[j] = r[j] * tw[(6 + j) * 16 + t];
-  // exchange 2: output j of lane L = 2 a + h at 9 L + j
-  cpx<T>* w2 = buf + 9 * t;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) w2[j] = r[j];
-  wave_sync();
-  const int a2 = t & 7, j0 = t >> 3;
-  const cpx<T>* r2 = buf + 18 * a2 + j0;
-#pragma unroll
-  for (int j1 = 0; j1 < 4; ++j1) {
-    const cpx<T> p0 = r2[2 * j1], p1 = r2[9 + 2 * j1];
-    r[j1] = p0 + p1;
-    r[j1 + 4] = p0 - p1;
-  }
-  wave_sync();
-}
-
-template <typename T>
-__device__ __forceinline__ void wave_fft64(cpx<T> (&r)[8], cpx<T>* __restrict__ buf,
-                                           const cpx<T>* __restrict__ tw, int t) {
-  Codelet<T, 8>::run(r, nullptr);
-#pragma unroll
-  for (int a = 1; a < 8; ++a) r[a] = r[a] * tw[(a - 1) * 8 + t];
-  // element (a, t) at 9 a + t; lane a then reads t = 0..7
-  cpx<T>* w1 = buf + t;
-#pragma unroll
-  for (int a = 0; a < 8; ++a) w1[9 * a] = r[a];
-  wave_sync();
-  const cpx<T>* r1 = buf + 9 * t;
-#pragma unroll
-  for (int t1 = 0; t1 < 8; ++t1) r[t1] = r1[t1];
-  wave_sync();
-  Codelet<T, 8>::run(r, nullptr);
-}
-
-// Outputs of the N = 192 and 96 transforms: P_h[a][j] (twiddled) sits at
-// PS h + b, b = a + 8 j < Q = 8 S / 3; lane t takes the radix-3 DFTs over h
-// of b = t, t + S, ... (< Q), X[b + Q c] for c = 0, 1, 2, writes them in
-// natural order (slots xw_nat), and reads back its own X[t + S m].
-template <typename T, int S, int PS>
-__device__ __forceinline__ void xw_radix3_out(cpx<T> (&r)[8], cpx<T>* __restrict__ buf,
-                                              int t) {
-  constexpr int Q = 8 * S / 3;          // radix-3 DFTs per row (64 at 192, 32 at 96)
-  constexpr int NB = (Q + S - 1) / S;   // per lane, the last one partial
-  const T s3 = T(0.86602540378443864676);  // sqrt(3) / 2
-  cpx<T> o[3 * NB];
-#pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    const int b = t + S * i;
-    if (b < Q) {
-      const cpx<T> p0 = buf[b], p1 = buf[PS + b], p2 = buf[2 * PS + b];
-      const cpx<T> sm = p1 + p2, df = p1 - p2;
-      const cpx<T> e = mul_i(df) * s3;
-      const cpx<T> base = p0 - sm * T(0.5);
-      o[3 * i] = p0 + sm;
-      o[3 * i + 1] = base - e;   // w3 = -1/2 - i sqrt(3)/2
-      o[3 * i + 2] = base + e;
-    }
-  }
-  wave_sync();
-#pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    const int b = t + S * i;
-    if (b < Q) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c) buf[xw_nat(b + Q * c)] = o[3 * i + c];
-    }
-  }
-  wave_sync();
-#pragma unroll
-  for (int m = 0; m < 8; ++m) r[m] = buf[xw_nat(t + S * m)];
-}
-
-template <typename T>
-__device__ __forceinline__ void wave_fft192(cpx<T> (&r)[8], cpx<T>* __restrict__ buf,
-                                            const cpx<T>* __restrict__ tw, int t) {
-  Codelet<T, 8>::run(r, nullptr);
-#pragma unroll
-  for (int a = 1; a < 8; ++a) r[a] = r[a] * tw[(a - 1) * 24 + t];
-  // exchange 1: element (a, t) at 25 a + t; lane 3 a + h reads t = h + 3 t1
-  cpx<T>* w1 = buf + t;
-#pragma unroll
-  for (int a = 0; a < 8; ++a) w1[25 * a] = r[a];
-  wave_sync();
-  const int a = t / 3, h = t - 3 * a;
-  const cpx<T>* r1 = buf + 25 * a + h;
-#pragma unroll
-  for (int t1 = 0; t1 < 8; ++t1) r[t1] = r1[3 * t1];
-  wave_sync();
-  Codelet<T, 8>::run(r, nullptr);
-#pragma unroll
-  for (int j = 1; j < 8; ++j) r[j] = r[j] * tw[(6 + j) * 24 + t];
-  // exchange 2: P_h[a][j] at 65 h + a + 8 j
-  cpx<T>* w2 = buf + 65 * h + a;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) w2[8 * j] = r[j];
-  wave_sync();
-  xw_radix3_out<T, 24, 65>(r, buf, t);
-  wave_sync();
-}
-
-template <typename T>
-__device__ __forceinline__ void wave_fft96(cpx<T> (&r)[8], cpx<T>* __restrict__ buf,
-                                           const cpx<T>* __restrict__ tw, int t) {
-  Codelet<T, 8>::run(r, nullptr);
-#pragma unroll
-  for (int a = 1; a < 8; ++a) r[a] = r[a] * tw[(a - 1) * 12 + t];
-  // exchange 1: element (a, t) at 13 a + t; lane 3 ap + h reads t = h + 3 t1
-  // of a = 2 ap (registers 0..3) and 2 ap + 1 (registers 4..7)
-  cpx<T>* w1 = buf + t;
-#pragma unroll
-  for (int a = 0; a < 8; ++a) w1[13 * a] = r[a];
-  wave_sync();
-  const int ap = t / 3, h = t - 3 * ap;
-  const cpx<T>* r1 = buf + 26 * ap + h;
-#pragma unroll
-  for (int t1 = 0; t1 < 4; ++t1) {
-    r[t1] = r1[3 * t1];
-    r[4 + t1] = r1[13 + 3 * t1];
-  }
-  wave_sync();
-  dft4_reg(r[0], r[1], r[2], r[3]);
-  dft4_reg(r[4], r[5], r[6], r[7]);
-#pragma unroll
-  for (int j = 1; j < 4; ++j) {
-    const cpx<T> f = tw[(6 + j) * 12 + t];
-    r[j] = r[j] * f;
-    r[4 + j] = r[4 + j] * f;
-  }
-  // exchange 2: P_h[a][j] at 33 h + a + 8 j
-  cpx<T>* w2 = buf + 33 * h + 2 * ap;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    w2[8 * j] = r[j];
-    w2[8 * j + 1] = r[4 + j];
-  }
-  wave_sync();
-  xw_radix3_out<T, 12, 33>(r, buf, t);
-  wave_sync();
-}
-
-template <typename T>
-__device__ __forceinline__ void wave_fft32(cpx<T> (&r)[8], cpx<T>* __restrict__ buf,
-                                           const cpx<T>* __restrict__ tw, int t) {
-  Codelet<T, 8>::run(r, nullptr);
-#pragma unroll
-  for (int a = 1; a < 8; ++a) r[a] = r[a] * tw[(a - 1) * 4 + t];
-  // element (a, t) at 4 a + t; lane L reads a = 2L (registers 0..3) and
-  // 2L + 1 (registers 4..7)
-  cpx<T>* w1 = buf + t;
-#pragma unroll
-  for (int a = 0; a < 8; ++a) w1[4 * a] = r[a];
-  wave_sync();
-  const cpx<T>* r1 = buf + 8 * t;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) r[i] = r1[i];
-  wave_sync();
-  dft4_reg(r[0], r[1], r[2], r[3]);
-  dft4_reg(r[4], r[5], r[6], r[7]);
-  // X[2L + 8 b] and X[2L + 1 + 8 b] into natural order, then X[t + 4 m]
-#pragma unroll
-  for (int b = 0; b < 4; ++b) {
-    buf[xw_nat(2 * t + 8 * b)] = r[b];
-    buf[xw_nat(2 * t + 1 + 8 * b)] = r[4 + b];
-  }
-  wave_sync();
-#pragma unroll
-  for (int m = 0; m < 8; ++m) r[m] = buf[xw_nat(t + 4 * m)];
-  wave_sync();
-}
-
-template <typename T, int N>
-__device__ __forceinline__ void wave_fft(cpx<T> (&r)[8], cpx<T>* __restrict__ buf,
-                                         const cpx<T>* __restrict__ tw, int t) {
-  if constexpr (N == 512)
-    wave_fft512<T>(r, buf, tw, t);
-  else if constexpr (N == 256)
-    wave_fft256<T>(r, buf, tw, t);
-  else if constexpr (N == 192)
-    wave_fft192<T>(r, buf, tw, t);
-  else if constexpr (N == 128)
-    wave_fft128<T>(r, buf, tw, t);
-  else if constexpr (N == 96)
-    wave_fft96<T>(r, buf, tw, t);
-  else if constexpr (N == 64)
-    wave_fft64<T>(r, buf, tw, t);
-  else
-    wave_fft32<T>(r, buf, tw, t);
-}
-
+// (rows of N points by wavefronts: xwave.hpp)
 // Forward transform of two finished real fields (b: none when !two), unpacked
 // into the r2c spectra of rows `row` of fields fa and fa + 1; nothing is
 // stored for a row past the end (valid false).
@@ -1109,7 +782,20 @@ template <typename T>
 void launch_y(const YArgs& a, bool big, bool inv, int mode, const cpx<T>* src, cpx<T>* dst,
               cpx<T>* dst2, long long sfs, long long dfs, int nplanes, int nfields,
               hipStream_t st) {
-  const int L = (a.lines == 8 && y_wide_tiles(a)) ? 8 : YL;
+  // Lines per tile: 4 or, at 512 points, 8 by choice for the compiled plans; 8
+  // over 256 threads for run-time plans up to Y_DYN8 points, whose stages of
+  // ny / radix butterflies per line would leave most threads idle with 4 lines
+  // (at 84 points 48 to 112 of 256), and whose tiles are then whole 128-byte
+  // lines (a channel solve of 32 x 32 x 33 with them: 1.64 -> 1.48 ms).  Above
+  // that two 8-line buffers would leave one workgroup per CU.
+  const bool compiled = y_wide_tiles(a) || (a.ny == 256 && plan_is(a.pl, {8, 8, 4})) ||
+                        (a.ny == 192 && plan_is(a.pl, {8, 8, 3})) ||
+                        (a.ny == 128 && plan_is(a.pl, {8, 8, 2})) ||
+                        (a.ny == 96 && plan_is(a.pl, {8, 4, 3})) ||
+                        (a.ny == 64 && plan_is(a.pl, {8, 8}));
+  constexpr int Y_DYN8 = 288;
+  const bool dyn8 = !compiled && a.ny <= Y_DYN8;
+  const int L = dyn8 || (a.lines == 8 && y_wide_tiles(a)) ? 8 : YL;
   const long long nlines = (long long)nplanes * a.nkxp;
   const long long ntiles = (nlines + L - 1) / L;
   const long long yg = a.grid > 0 ? a.grid : Y_GRID;
@@ -1119,71 +805,56 @@ void launch_y(const YArgs& a, bool big, bool inv, int mode, const cpx<T>* src, c
   if (gx < yg && gx % 64) gx = std::min(yg, (gx + 63) / 64 * 64);
   dim3 grid((unsigned)gx, nfields);
   const size_t sh = y_lds_bytes(a.ny, a.pl.tsize, sizeof(cpx<T>), L);
-  const int need = (a.ny + YNT / YL - 1) / (YNT / YL);
   const int iv = inv ? 1 : 0;
-#define FCNS_YL(FPV, OWNV, LV)                                                                \
+#define FCNS_YN(FPV, OWNV, LV, NTV)                                                         \
   do {                                                                                      \
     if (a.noprefetch)                                                                       \
-      FCNS_LAUNCH((k_y<T, FPV, OWNV, false, LV>), grid, dim3(64 * LV), sh, st, a, src, dst,   \
+      FCNS_LAUNCH((k_y<T, FPV, OWNV, false, LV, NTV>), grid, dim3(NTV), sh, st, a, src, dst, \
                   dst2, sfs, dfs, nlines, iv, mode);                                        \
     else                                                                                    \
-      FCNS_LAUNCH((k_y<T, FPV, OWNV, true, LV>), grid, dim3(64 * LV), sh, st, a, src, dst,    \
+      FCNS_LAUNCH((k_y<T, FPV, OWNV, true, LV, NTV>), grid, dim3(NTV), sh, st, a, src, dst,  \
                   dst2, sfs, dfs, nlines, iv, mode);                                        \
   } while (0)
-#define FCNS_Y(FPV, OWNV) FCNS_YL(FPV, OWNV, YL)
+#define FCNS_Y(FPV, OWNV) FCNS_YN(FPV, OWNV, YL, YNT)
   if (y_wide_tiles(a)) {
     using P512 = SPlan<8, 8, 8>;
     if (L == 8)
-      FCNS_YL(P512, 8, 8);
+      FCNS_YN(P512, 8, 8, 512);
     else
       FCNS_Y(P512, 8);
-  } else if (a.ny == 256 && plan_is(a.pl, {8, 8, 4})) {
+  } else if (compiled && a.ny == 256) {
     using P256 = SPlan<8, 8, 4>;
     FCNS_Y(P256, 4);
-  } else if (a.ny == 192 && plan_is(a.pl, {8, 8, 3})) {
+  } else if (compiled && a.ny == 192) {
     using P192 = SPlan<8, 8, 3>;
     FCNS_Y(P192, 4);
-  } else if (a.ny == 128 && plan_is(a.pl, {8, 8, 2})) {
+  } else if (compiled && a.ny == 128) {
     using P128 = SPlan<8, 8, 2>;
     FCNS_Y(P128, 4);
-  } else if (a.ny == 96 && plan_is(a.pl, {8, 4, 3})) {
+  } else if (compiled && a.ny == 96) {
     using P96 = SPlan<8, 4, 3>;
     FCNS_Y(P96, 4);
-  } else if (a.ny == 64 && plan_is(a.pl, {8, 8})) {
+  } else if (compiled) {
     using P64 = SPlan<8, 8>;
     FCNS_Y(P64, 4);
+  } else if (dyn8) {
+    if (big) {
+      if (a.ny <= 128) FCNS_YN(DynPlan<true>, 4, 8, 256); else FCNS_YN(DynPlan<true>, 9, 8, 256);
+    } else {
+      if (a.ny <= 128) FCNS_YN(DynPlan<false>, 4, 8, 256); else FCNS_YN(DynPlan<false>, 9, 8, 256);
+    }
   } else if (big) {
-    if (need <= 4) FCNS_Y(DynPlan<true>, 4); else if (need <= 8) FCNS_Y(DynPlan<true>, 8); else FCNS_Y(DynPlan<true>, 16);
+    if (a.ny <= 512) FCNS_Y(DynPlan<true>, 8); else FCNS_Y(DynPlan<true>, 16);
   } else {
-    if (need <= 4) FCNS_Y(DynPlan<false>, 4); else if (need <= 8) FCNS_Y(DynPlan<false>, 8); else FCNS_Y(DynPlan<false>, 16);
+    if (a.ny <= 512) FCNS_Y(DynPlan<false>, 8); else FCNS_Y(DynPlan<false>, 16);
   }
 #undef FCNS_Y
-#undef FCNS_YL
+#undef FCNS_YN
 }
 template void launch_y<double>(const YArgs&, bool, bool, int, const cpx<double>*, cpx<double>*,
                                cpx<double>*, long long, long long, int, int, hipStream_t);
 template void launch_y<float>(const YArgs&, bool, bool, int, const cpx<float>*, cpx<float>*,
                               cpx<float>*, long long, long long, int, int, hipStream_t);
-
-void launch_x_r2c(const XArgs& a, bool big, const double* phys, cpx<double>* xy, long long pfs,
-                  long long xfs, long long nrows, int nfields, hipStream_t st) {
-  dim3 grid((unsigned)((nrows + XR - 1) / XR), nfields);
-  const size_t sh = ((size_t)a.pl.tsize + 2 * XL * x_ls(a.nx)) * sizeof(cpx<double>);
-  if (big)
-    FCNS_LAUNCH((k_x_r2c<double, true>), grid, dim3(XNT), sh, st, a, phys, xy, pfs, xfs, nrows);
-  else
-    FCNS_LAUNCH((k_x_r2c<double, false>), grid, dim3(XNT), sh, st, a, phys, xy, pfs, xfs, nrows);
-}
-
-void launch_x_c2r(const XArgs& a, bool big, const cpx<double>* xy, double* phys, long long xfs,
-                  long long pfs, long long nrows, int nfields, hipStream_t st) {
-  dim3 grid((unsigned)((nrows + XR - 1) / XR), nfields);
-  const size_t sh = ((size_t)a.pl.tsize + 2 * XL * x_ls(a.nx)) * sizeof(cpx<double>);
-  if (big)
-    FCNS_LAUNCH((k_x_c2r<double, true>), grid, dim3(XNT), sh, st, a, xy, phys, xfs, pfs, nrows);
-  else
-    FCNS_LAUNCH((k_x_c2r<double, false>), grid, dim3(XNT), sh, st, a, xy, phys, xfs, pfs, nrows);
-}
 
 template <typename T, class FP, int RR, int NT, int CC>
 static void launch_x_nl_v(const XArgs& a, const cpx<T>* xyb, cpx<T>* nl, long long fs,
@@ -1194,15 +865,11 @@ static void launch_x_nl_v(const XArgs& a, const cpx<T>* xyb, cpx<T>* nl, long lo
               nfields);
 }
 
-static bool x_wave_rows(int nx) {
-  return nx == 512 || nx == 256 || nx == 192 || nx == 128 || nx == 96 || nx == 64 ||
-         nx == 32;
-}
-
 bool x_reads_blocked(const XArgs& a) { return x_wave_rows(a.nx) && a.variant == 0; }
 
 // nx = 512, 256, 192, 128, 96, 64 and 32: wave-level rows (variant 0) or the tiled kernels; other
-// nx: 4 rows x 256 threads (variant 0, 1) or 8 rows x 512 threads (variant 2),
+// nx: three quantities at a time over 8 rows (variant 0, short rows), 4 rows x
+// 256 threads (variant 0 beyond those, and 1) or 8 rows x 512 threads (variant 2),
 // with compile-time plans for 512 and 256; nx <= 256: 8 rows x nx threads
 // (variant 3)
 template <typename T>
@@ -1279,6 +946,17 @@ void launch_x_nl(const XArgs& a, bool big, const cpx<T>* xyb, cpx<T>* nl, long l
     else
       FCNS_XW(k_x_nlw, 3, 32);
 #undef FCNS_XW
+  } else if (a.variant == 0 && a.nx <= X3_MAXNX && 2 * x3_lds<T>(a) <= 160 * 1024) {
+    // (two workgroups per CU: FP64 rows up to 160 points)
+    dim3 grid((unsigned)((nrows + 7) / 8));
+#define FCNS_X3(NFV, BV)                                                                      \
+  FCNS_LAUNCH((k_x_nl3<T, NFV, BV>), grid, dim3(X3_NT), x3_lds<T>(a), st, a, xyb, nl, fs, nrows)
+    if (nfields == 4) {
+      if (big) FCNS_X3(4, true); else FCNS_X3(4, false);
+    } else {
+      if (big) FCNS_X3(3, true); else FCNS_X3(3, false);
+    }
+#undef FCNS_X3
   } else if (a.nx == 512 && plan_is(a.pl, {8, 8, 8}))
     launch_x_nl_v<T, SPlan<8, 8, 8>, 4, 256, 2>(a, xyb, nl, fs, nrows, nfields, st);
   else if (a.nx == 256 && plan_is(a.pl, {8, 8, 4}))

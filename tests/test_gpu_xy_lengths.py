@@ -1,0 +1,89 @@
+"""The x and y transforms over row lengths: wavefront rows, LDS tiles (with their
+radix remainders, prime factors above 7 and the edges where the tile shape
+changes: 160 and 162 points in x, 256 and 258, 288 and 290 in y), row counts
+that leave partial tiles, against the FP64 oracle.
+
+Bar 1e-11 as for every solver output: these transforms add a few 1e-16 to the
+continuation's rounding (d = 5: the oracle's spectrum moves 1e-12 to 5e-12 for a
+1e-15 relative change of its input)."""
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle.ns import Oracle, Problem
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def fcns():
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    import paper_2002_01392_amd as P
+    P.load_library()
+    return P
+
+
+def rel_l2(a, b):
+    a = a.detach().cpu().numpy() if hasattr(a, "detach") else np.asarray(a)
+    nb = np.linalg.norm(b)
+    return float(np.linalg.norm(a - b) / (nb if nb > 0 else 1.0))
+
+
+def _fields(nx, ny, nz, seed):
+    v = np.stack([W.smooth_field(nx, ny, nz, 2.0, 3.0, 1.3, seed + i, kmax=2) for i in range(3)])
+    th = W.smooth_field(nx, ny, nz, 2.0, 3.0, 1.3, seed + 9, kmax=2)
+    # content at every mode, the Nyquist ones included
+    v += 0.1 * W.white_field(v.shape, seed + 20)
+    return v, th + 0.1 * W.white_field(th.shape, seed + 21)
+
+
+@pytest.mark.parametrize("nx,ny,theta", [
+    (4, 6, True), (10, 4, False), (30, 14, True), (84, 6, False), (120, 10, True),
+    (158, 8, False), (160, 6, True), (162, 6, True), (256, 6, True), (258, 4, False),
+    (512, 4, True), (96, 12, True), (32, 10, False), (6, 84, True), (8, 90, False),
+    (6, 256, True), (4, 286, False), (6, 288, True), (4, 290, True), (4, 512, False),
+    (6, 518, True)])
+def test_nonlinear_term_and_state(fcns, nx, ny, theta):
+    nz = 11   # 11 ny rows: partial tiles of 8 and 16 rows
+    C = 15
+    s = fcns.Solver(nx, ny, nz, 2.0, 3.0, 1.3, 0.01, C=C, boussinesq=theta, kappa=0.01,
+                    gamma=1.0)
+    v, th = _fields(nx, ny, nz, 7 * nx + ny)
+    tv, tt = torch.from_numpy(v), torch.from_numpy(th) if theta else None
+    nlv, nlt = s.rhs_nonlinear(tv, tt)
+    s.set_state(tv, tt)
+    back, bth, _ = s.get_state()
+    torch.cuda.synchronize()
+    o = Oracle(Problem(nx=nx, ny=ny, nz=nz, lx=2.0, ly=3.0, lz=1.3, nu=0.01, C=C,
+                       boussinesq=theta, kappa=0.01, gamma=1.0))
+    rv, rt = o.rhs_nonlinear(v, th if theta else None)
+    o.set_state(v, th if theta else None)
+    sv, st, _ = o.get_state()
+    assert rel_l2(nlv, rv) < 1e-11
+    assert rel_l2(back, sv) < 1e-11
+    if theta:
+        assert rel_l2(nlt, rt) < 1e-11
+        assert rel_l2(bth, st) < 1e-11
+    s.close()
+
+
+@pytest.mark.parametrize("nx,ny", [(30, 14), (120, 84), (174, 10), (6, 290)])
+def test_mixed_precision_step(fcns, nx, ny):
+    w = W.rayleigh_benard(nx, ny, 33, 1e5, C=25, dt=1e-3, steps=2, seed=31, noise_rms=1e-2,
+                          kmax=2, mmax=3, perturbation="curl_eigen")
+    w = W.replace(w, dt=W.stable_dt(w))
+    v0, th0 = w.initial_state()
+    s = fcns.Solver.from_workload(w, precision="mixed")
+    s.set_state(torch.from_numpy(v0), torch.from_numpy(th0))
+    s.rk_step(w.dt, 2)
+    v, th, _ = s.get_state()
+    s.synchronize()
+    o = Oracle(Problem(**w.problem_kwargs()))
+    o.set_state(v0, th0)
+    o.rk_step(w.dt, 2)
+    rv, rth, _ = o.get_state()
+    assert rel_l2(v, rv) < 2e-6 and rel_l2(th, rth) < 2e-6
+    s.close()
