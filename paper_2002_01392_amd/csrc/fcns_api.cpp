@@ -29,6 +29,12 @@ struct fcns_ctx {
   cpx<double>* twy = nullptr;
   cpx<double>* rootz = nullptr; // N' roots of unity (wall sums)
   bool mixed = false;           // FP32 transforms and mixed-space arrays in rk_step
+  double* ptz = nullptr;        // cosines and sines of stages of primes above 7, or null
+  double* ptx = nullptr;
+  double* pty = nullptr;
+  float* ptz_f = nullptr;
+  float* ptx_f = nullptr;
+  float* pty_f = nullptr;
   cpx<float>* twz_f = nullptr;  // the plan tables rounded to FP32 (mixed precision)
   cpx<float>* twx_f = nullptr;
   cpx<float>* twy_f = nullptr;
@@ -150,13 +156,22 @@ static fcns_status check_launch(fcns_ctx* c, const char* what) {
 }
 
 // ---------------------------------------------------------------- plans
-// Radices 8 first, then 4, 2 and odd primes ascending (at most 12 stages).
+// Primes above 7 first (their stage then needs no twiddle pass), then radices 8,
+// 4, 2 and odd primes ascending (at most 12 stages).
 // Also lays out the twiddle table: per stage with ns > 1 the factors
 // w^{m k} = exp(-2 pi i m k / (ns R)) as [m-1][k], and per odd-radix stage its
 // R roots exp(-2 pi i q / R).
 static std::vector<int> default_radices(int n) {
   int m = n;
   std::vector<int> rs;
+  for (int p = 11; p <= m; p += 2) {
+    // (a composite p has no factor left in m unless one of 3, 5, 7 divides it)
+    if (p % 3 == 0 || p % 5 == 0 || p % 7 == 0) continue;
+    while (m % p == 0) {
+      rs.push_back(p);
+      m /= p;
+    }
+  }
   while (m % 8 == 0) { rs.push_back(8); m /= 8; }
   while (m % 4 == 0) { rs.push_back(4); m /= 4; }
   while (m % 2 == 0) { rs.push_back(2); m /= 2; }
@@ -207,6 +222,29 @@ static bool make_plan_order(int n, const std::vector<int>& rs, FFTPlan& pl, bool
   return true;
 }
 
+// The cosines and sines of the plan's stages of primes above 7 (prime_columns),
+// and each stage's place in them.
+static std::vector<double> prime_tables(FFTPlan& pl) {
+  std::vector<double> t;
+  const long double pi = 3.141592653589793238462643383279502884L;
+  for (int s = 0; s < pl.nst; ++s) {
+    const int R = pl.r[s];
+    pl.poff[s] = -1;
+    if (R <= 8 || R % 2 == 0 || R > PRIME_MAX) continue;
+    pl.poff[s] = (int)t.size();
+    const int H = (R - 1) / 2, kb = prime_kb(R), ld = prime_ld(R);
+    for (int g = 0; g < prime_groups(R); ++g)
+      for (int q = 1; q <= H; ++q)
+        for (int sn = 0; sn < 2; ++sn)
+          for (int i = 0; i < ld; ++i) {
+            const int k = 1 + g * kb + i;
+            const long double a = 2.0L * pi * (long double)((long long)q * k % R) / R;
+            t.push_back(i < kb && k <= H ? (double)(sn ? sinl(a) : cosl(a)) : 0.0);
+          }
+  }
+  return t;
+}
+
 static bool make_plan(int n, FFTPlan& pl, bool& big, std::vector<cpx<double>>& table) {
   return make_plan_order(n, default_radices(n), pl, big, table);
 }
@@ -252,12 +290,24 @@ static fcns_status alloc(fcns_ctx* c, cpx<double>** p, long long n) {
   return FCNS_OK;
 }
 
+// The prime tables of a plan (nothing for one without primes above 7): d in
+// FP64, f rounded to FP32 when wanted.
+static fcns_status upload_primes(fcns_ctx* c, FFTPlan& pl, double** d, float** f) {
+  const std::vector<double> t = prime_tables(pl);
+  if (t.empty()) return FCNS_OK;
+  const std::vector<float> tf(t.begin(), t.end());
+  fcns_status st = upload(c, d, t.data(), t.size());
+  if (st == FCNS_OK && c->mixed) st = upload(c, f, tf.data(), tf.size());
+  return st;
+}
+
 static void free_all(fcns_ctx* c) {
   if (c->graph) (void)hipGraphExecDestroy(c->graph);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
   for (hipEvent_t e : c->evpool) (void)hipEventDestroy(e);
   c->evpool.clear();
-  void* ps[] = {c->twz, c->twx, c->twy, c->twz_f, c->twx_f, c->twy_f, c->rootz, c->fcM, c->sigx, c->sigy, c->sigz, c->P, c->Q,
+  void* ps[] = {c->twz, c->twx, c->twy, c->twz_f, c->twx_f, c->twy_f, c->ptz, c->ptx, c->pty, c->ptz_f,
+                c->ptx_f, c->pty_f, c->rootz, c->fcM, c->sigx, c->sigy, c->sigz, c->P, c->Q,
                 c->VS, c->MV, c->MVT, c->XYB, c->NLB, c->PM, c->GW, c->GWT, c->DG};
   for (void* p : ps)
     if (p) (void)hipFree(p);
@@ -270,6 +320,7 @@ static ZArgs zargs(const fcns_ctx* c, bool f32 = false) {
   memset(&a, 0, sizeof(a));  // padding too: batch descriptors are compared bytewise
   a.g = c->g;
   a.pl = c->plz;
+  a.pl.prime = f32 ? (const void*)c->ptz_f : (const void*)c->ptz;
   a.tw = f32 ? (const void*)c->twz_f : (const void*)c->twz;
   a.tw64 = c->rootz;
   a.fc = c->fcM;
@@ -286,6 +337,7 @@ static YArgs yargs(const fcns_ctx* c, bool f32 = false, bool dy = false) {
   a.nkxp = c->g.nkxp;
   a.kys = c->g.kys;
   a.pl = c->ply;
+  a.pl.prime = f32 ? (const void*)c->pty_f : (const void*)c->pty;
   a.tw = f32 ? (const void*)c->twy_f : (const void*)c->twy;
   a.grid = dy ? c->ygrid1 : c->ygrid;
   a.noprefetch = dy ? c->ynopf1 : c->ynopf;
@@ -300,6 +352,7 @@ static XArgs xargs(const fcns_ctx* c, bool f32 = false) {
   a.ny = c->g.ny;
   a.kxs = c->g.kxs;
   a.pl = c->plx;
+  a.pl.prime = f32 ? (const void*)c->ptx_f : (const void*)c->ptx;
   a.tw = f32 ? (const void*)c->twx_f : (const void*)c->twx;
   a.variant = c->xvar;
   return a;
@@ -403,7 +456,10 @@ extern "C" fcns_status fcns_create(const fcns_problem* prob, void* hip_stream, f
       return st;
     }
   }
-  if ((st = upload(c, &c->twz, twz.data(), twz.size())) ||
+  if ((st = upload_primes(c, c->plz, &c->ptz, &c->ptz_f)) ||
+      (st = upload_primes(c, c->plx, &c->ptx, &c->ptx_f)) ||
+      (st = upload_primes(c, c->ply, &c->pty, &c->pty_f)) ||
+      (st = upload(c, &c->twz, twz.data(), twz.size())) ||
       (st = upload(c, &c->twx, twx.data(), twx.size())) ||
       (st = upload(c, &c->twy, twy.data(), twy.size())) ||
       (st = upload(c, &c->rootz, rz.data(), rz.size())) ||
@@ -473,8 +529,20 @@ extern "C" fcns_status fcns_footprint(const fcns_problem* p, int64_t* bytes) {
   const long long nf = p->boussinesq ? 4 : 3;
   // P, Q, VS; MV, MVT, XYB, NLB, PM; GW, GWT (complex128), plus tables
   const long long elems = 3 * nf * S + (2 * nf + 2 * nf + 3 * nf + nf + 1) * M + 8 * npen;
-  const long long tables = 16LL * (4LL * (p->nx + p->ny + p->nz + p->fc_C) + 4096) +
+  // the cosines and sines of each length's primes above 7
+  auto primes = [&](long long n) {
+    long long b = 0;
+    for (long long q = 2; n > 1; ++q)
+      while (n % q == 0) {
+        if (q > 7) b += 8LL * prime_table((int)q);
+        n /= q;
+      }
+    return b;
+  };
+  long long tables = 16LL * (4LL * (p->nx + p->ny + p->nz + p->fc_C) + 4096) +
                            8LL * p->fc_C * p->fc_d;
+  tables += (primes(p->nx) + primes(p->ny) + primes(p->nz + p->fc_C)) *
+            (p->precision == FCNS_MIXED ? 3 : 2) / 2;
   *bytes = (int64_t)(elems * 16 + tables);
   return FCNS_OK;
 }
@@ -935,18 +1003,30 @@ static fcns_status set_z_plan(fcns_ctx* c, const std::vector<int>& rs) {
   if (!make_plan_order(c->g.npr, rs, pl, big, t)) return fail(c, FCNS_EINVAL, "bad z plan");
   cpx<double>* d = nullptr;
   cpx<float>* f = nullptr;
+  double* pd = nullptr;
+  float* pf = nullptr;
   fcns_status st;
-  if ((st = upload(c, &d, t.data(), t.size()))) return st;
+  if ((st = upload_primes(c, pl, &pd, &pf)) || (st = upload(c, &d, t.data(), t.size()))) {
+    if (pd) (void)hipFree(pd);
+    if (pf) (void)hipFree(pf);
+    return st;
+  }
   if (c->mixed) {
     std::vector<cpx<float>> tf(t.size());
     for (size_t i = 0; i < t.size(); ++i) tf[i] = mk((float)t[i].x, (float)t[i].y);
     if ((st = upload(c, &f, tf.data(), tf.size()))) {
       (void)hipFree(d);
+      if (pd) (void)hipFree(pd);
+      if (pf) (void)hipFree(pf);
       return st;
     }
   }
   (void)hipStreamSynchronize(c->stream);
   (void)hipFree(c->twz);
+  if (c->ptz) (void)hipFree(c->ptz);
+  if (c->ptz_f) (void)hipFree(c->ptz_f);
+  c->ptz = pd;
+  c->ptz_f = pf;
   if (c->twz_f) (void)hipFree(c->twz_f);
   c->twz = d;
   c->twz_f = f;

@@ -37,7 +37,26 @@ struct FFTPlan {
   int toff[FFT_MAX_STAGES];  // stage twiddles [m-1][k] (ns > 1), else -1
   int coff[FFT_MAX_STAGES];  // roots of unity of odd radices, else -1
   int tsize;                 // complex entries of the whole table
+  // odd primes above 7: cosines and sines of the column form (prime_columns), in
+  // the transform's type, stage s at prime + poff[s]; null or -1: the pair form
+  const void* prime;
+  int poff[FFT_MAX_STAGES];
 };
+
+// Output pairs per wavefront pass of the column form, and its table: for each
+// group of prime_kb pairs and each input pair q = 1..H (H = (R - 1) / 2) a row
+// of prime_ld cosines cos(2 pi q k / R), then as many sines.
+__host__ __device__ constexpr int prime_kb(int R) { return R <= 31 ? 4 : 7; }
+__host__ __device__ constexpr int prime_ld(int R) { return R <= 31 ? 4 : 8; }
+__host__ __device__ constexpr int prime_groups(int R) {
+  return ((R - 1) / 2 + prime_kb(R) - 1) / prime_kb(R);
+}
+// (none above PRIME_MAX: it grows with R^2, and one line's pairs then occupy the
+// pair form's threads)
+constexpr int PRIME_MAX = 256;
+__host__ __device__ constexpr int prime_table(int R) {
+  return R > PRIME_MAX ? 0 : prime_groups(R) * ((R - 1) / 2) * 2 * prime_ld(R);
+}
 
 // ---------------------------------------------------------------- codelets
 template <typename T>
@@ -302,6 +321,19 @@ __device__ __forceinline__ void fft_stage(const cpx<T>* __restrict__ src, cpx<T>
   }
 }
 
+// The value of lane ^ 1 (DPP quad_perm [1, 0, 3, 2]).
+__device__ __forceinline__ float lane_xor1(float v) {
+  return __builtin_bit_cast(
+      float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xf, 0xf, true));
+}
+__device__ __forceinline__ double lane_xor1(double v) {
+  typedef int i2 __attribute__((ext_vector_type(2)));
+  i2 w = __builtin_bit_cast(i2, v);
+  w.x = __builtin_amdgcn_update_dpp(0, w.x, 0xB1, 0xf, 0xf, true);
+  w.y = __builtin_amdgcn_update_dpp(0, w.y, 0xB1, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, w);
+}
+
 // Any odd prime R > 7 at run time, spread over the workgroup: a line of n
 // points has only n / R butterflies of this radix, too few to occupy the
 // threads, and one whole R-point DFT per thread would not fit in registers.
@@ -340,6 +372,8 @@ __device__ __forceinline__ void prime_outputs(const cpx<T>* __restrict__ src,
       im[i] = zero<T>();
       qk[i] = 0;
     }
+    // (unrolled over a constant length this loop would spill hundreds of registers)
+#pragma unroll 1
     for (int q = 1; q <= H; ++q) {
       const cpx<T> xa = S(q), xb = S(R - q);
       const cpx<T> ps = xa + xb, ms = xa - xb;
@@ -366,13 +400,81 @@ __device__ __forceinline__ void prime_outputs(const cpx<T>* __restrict__ src,
   }
 }
 
+// The column form of the same stage: a lane is one column, the real or imaginary
+// part of one butterfly, and a wavefront forms prime_kb output pairs of 64
+// columns, so that the roots are wave-uniform and come through the scalar
+// cache.  With a_q, b_q the sums and differences of the column's inputs,
+// P_k = x_0 + sum a_q cos, Q_k = sum b_q sin; the two parts of a butterfly sit in
+// neighbouring lanes and exchange their Q:
+//   Re X_k = P_re + Q_im, Im X_k = P_im - Q_re, X_{R-k} with the signs swapped.
+// Two multiply-adds per pair and input against an LDS read of each input per
+// prime_kb pairs; the pair form reads five roots from LDS at indices stepped
+// modulo R for every twenty multiply-adds.
+template <typename T, bool PAD, int KB, int LD>
+__device__ __forceinline__ void prime_columns(const cpx<T>* __restrict__ src,
+                                              cpx<T>* __restrict__ dst, int R, int L, int es,
+                                              int ls, int nr, int ns, float rcp,
+                                              const void* __restrict__ tab, int tid, int nt) {
+  using CT = const __attribute__((address_space(4))) T;
+  const int H = (R - 1) / 2, ngrp = (H + KB - 1) / KB;
+  const int nb = L * nr, ncb = (2 * nb + 63) / 64;
+  const int lane = tid & 63, nw = nt >> 6;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const T* S0 = reinterpret_cast<const T*>(src);
+  T* D0 = reinterpret_cast<T*>(dst);
+  for (int item = wv; item < ncb * ngrp; item += nw) {
+    const int grp = item / ncb, cb = item - grp * ncb;
+    const int col = cb * 64 + lane, part = col & 1;
+    const bool ok = col < 2 * nb;
+    const int b = ok ? col >> 1 : nb - 1;
+    const int l = b % L, j = b / L;
+    const int k = fast_mod(j, ns, rcp);
+    auto S = [&](int m) -> T { return S0[2 * lds_pos<PAD>(l, j + m * nr, es, ls) + part]; };
+    const T x0 = S(0);
+    T sum = x0, P[KB], Q[KB];
+#pragma unroll
+    for (int i = 0; i < KB; ++i) {
+      P[i] = x0;
+      Q[i] = T(0);
+    }
+    CT* c = reinterpret_cast<CT*>(reinterpret_cast<uintptr_t>(tab)) + grp * H * 2 * LD;
+#pragma unroll 1
+    for (int q = 1; q <= H; ++q, c += 2 * LD) {
+      const T xa = S(q), xb = S(R - q);
+      const T ps = xa + xb, ms = xa - xb;
+      sum += ps;
+#pragma unroll
+      for (int i = 0; i < KB; ++i) {
+        P[i] += ps * c[i];
+        Q[i] += ms * c[LD + i];
+      }
+    }
+    const int o = (j - k) * R + k;
+    auto D = [&](int m) -> T& { return D0[2 * lds_pos<PAD>(l, o + m * ns, es, ls) + part]; };
+    if (ok && grp == 0) D(0) = sum;
+    const T sg = part ? T(-1) : T(1);
+#pragma unroll
+    for (int i = 0; i < KB; ++i) {
+      const T qo = sg * lane_xor1(Q[i]);
+      const int kk = 1 + grp * KB + i;
+      if (ok && kk <= H) {
+        D(kk) = P[i] + qo;
+        D(R - kk) = P[i] - qo;
+      }
+    }
+  }
+}
+
 constexpr int PRIME_PG = 5;
 
-template <typename T, bool PAD>
+// COLS: the plan surely has its prime table (compiled plans); a run-time plan
+// without one (the context-free derivative) runs the pair form.
+template <typename T, bool PAD, bool COLS>
 __device__ __forceinline__ void fft_stage_prime(cpx<T>* __restrict__ src, cpx<T>* __restrict__ dst,
                                                 int R, int L, int es, int ls, int n, int ns,
                                                 const cpx<T>* __restrict__ tws,
-                                                const cpx<T>* __restrict__ cw, int tid, int nt) {
+                                                const cpx<T>* __restrict__ cw, const void* prime,
+                                                int poff, int tid, int nt) {
   const int nr = n / R;
   const int nb = L * nr;
   const float rcp = 1.0f / (float)ns;
@@ -386,10 +488,24 @@ __device__ __forceinline__ void fft_stage_prime(cpx<T>* __restrict__ src, cpx<T>
     }
     __syncthreads();
   }
+  // The pair form where its items fill seven eighths of the threads (6 x 47 points
+  // of 8 lines: 240 of 256; stage A 0.77 ms against 0.82 with columns at 256 x 256
+  // x 257), the column form below that (2 x 53: 96 of 256; stage A 0.144 -> 0.109
+  // ms, back transforms 0.095 -> 0.069 at 120 x 84 x 81; 6 x 31: 0.406 -> 0.364 and
+  // 0.253 -> 0.228 at 160 x 160 x 161).
   const int H = (R - 1) / 2;
-  if (2 * nb * ((H + PRIME_PG - 1) / PRIME_PG) >= nt)
+  const bool pairs = 8 * nb * ((H + PRIME_PG - 1) / PRIME_PG) >= 7 * nt;
+  if (!pairs && (COLS || (prime && poff >= 0))) {
+    const T* tab = reinterpret_cast<const T*>(prime) + poff;
+    if (prime_kb(R) == 4)
+      prime_columns<T, PAD, 4, 4>(src, dst, R, L, es, ls, nr, ns, rcp, tab, tid, nt);
+    else
+      prime_columns<T, PAD, 7, 8>(src, dst, R, L, es, ls, nr, ns, rcp, tab, tid, nt);
+    return;
+  }
+  if (pairs || 2 * nb * ((H + PRIME_PG - 1) / PRIME_PG) >= nt)
     prime_outputs<T, PAD, PRIME_PG>(src, dst, R, L, es, ls, nr, ns, rcp, cw, tid, nt);
-  else
+  else if constexpr (!COLS)
     prime_outputs<T, PAD, 1>(src, dst, R, L, es, ls, nr, ns, rcp, cw, tid, nt);
 }
 
@@ -420,7 +536,9 @@ __device__ __forceinline__ cpx<T>* fft_fwd(cpx<T>* buf0, cpx<T>* buf1, int es, i
       case 7: fft_stage<T, 7, PAD>(src, dst, L, es, ls, n, ns, tws, cw, tid, nt); break;
       case 8: fft_stage<T, 8, PAD>(src, dst, L, es, ls, n, ns, tws, cw, tid, nt); break;
       default:
-        if constexpr (BIG) fft_stage_prime<T, PAD>(src, dst, r, L, es, ls, n, ns, tws, cw, tid, nt);
+        if constexpr (BIG)
+          fft_stage_prime<T, PAD, false>(src, dst, r, L, es, ls, n, ns, tws, cw, pl.prime, pl.poff[s], tid,
+                                  nt);
         break;
     }
     __syncthreads();
@@ -488,7 +606,7 @@ __device__ __forceinline__ cpx<T>* sfft_from(cpx<T>* src, cpx<T>* dst, int es, i
   const cpx<T>* tws = tw + (NS > 1 ? pl.toff[S] : 0);
   const cpx<T>* cw = tw + ((R & 1) ? pl.coff[S] : 0);
   if constexpr (R % 2 == 1 && R > 8)  // odd primes: the cooperative stage, constant sizes
-    fft_stage_prime<T, PAD>(src, dst, R, L, es, ls, N, NS, tws, cw, tid, NT);
+    fft_stage_prime<T, PAD, true>(src, dst, R, L, es, ls, N, NS, tws, cw, pl.prime, pl.poff[S], tid, NT);
   else
     sfft_stage<T, R, NS, N, L, NT, PAD>(src, dst, es, ls, tws, cw, tid);
   __syncthreads();

@@ -839,9 +839,13 @@ void launch_y(const YArgs& a, bool big, bool inv, int mode, const cpx<T>* src, c
     FCNS_Y(P64, 4);
   } else if (dyn8) {
     if (big) {
-      if (a.ny <= 128) FCNS_YN(DynPlan<true>, 4, 8, 256); else FCNS_YN(DynPlan<true>, 9, 8, 256);
+      if (a.ny <= 128) FCNS_YN(DynPlan<true>, 4, 8, 256);
+      else if (a.ny <= 192) FCNS_YN(DynPlan<true>, 6, 8, 256);
+      else FCNS_YN(DynPlan<true>, 9, 8, 256);
     } else {
-      if (a.ny <= 128) FCNS_YN(DynPlan<false>, 4, 8, 256); else FCNS_YN(DynPlan<false>, 9, 8, 256);
+      if (a.ny <= 128) FCNS_YN(DynPlan<false>, 4, 8, 256);
+      else if (a.ny <= 192) FCNS_YN(DynPlan<false>, 6, 8, 256);
+      else FCNS_YN(DynPlan<false>, 9, 8, 256);
     }
   } else if (big) {
     if (a.ny <= 512) FCNS_Y(DynPlan<true>, 8); else FCNS_Y(DynPlan<true>, 16);

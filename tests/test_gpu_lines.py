@@ -128,3 +128,40 @@ def test_fc_derivative_wavefront_lengths(fcns, npr, C, n, order):
         gaps[idx.ravel()] = False
         assert np.all(got[gaps] == 7.0), (ps, ls)
     s.close()
+
+
+# lengths with primes above 7 (one stage of them, two, a square), both forms of the
+# prime stage: few butterflies (columns), many (pairs), and the longest line
+@pytest.mark.parametrize("npr,C", [(22, 5), (26, 15), (58, 25), (62, 15), (106, 25), (154, 25),
+                                   (186, 25), (218, 25), (242, 25), (254, 25), (282, 25),
+                                   (286, 25), (442, 25), (502, 25)])
+@pytest.mark.parametrize("order", [1, 2])
+def test_fc_derivative_prime_lengths(fcns, npr, C, order):
+    nz, d = npr - C, 5
+    table, bar = None, 1e-11
+    if C == 5:   # (no stored table: a smooth one)
+        q, a = np.eye(d), np.zeros((C, d))
+        a[:, d - 1] = np.linspace(1.0, 0.0, C + 2)[1:-1] ** 2
+        table = np.concatenate([q.ravel(), a.ravel()])
+    s = fcns.Solver(8, 8, nz, 1.0, 1.0, 1.7, 0.0, d=d, C=C, table=table)
+    f = _lines(nz, 21, 11 * npr)
+    if table is None:
+        ref = fc_derivative_lines(f, d, C, 1.7, order)
+        # k^2 of the longest lines amplifies the continuation's rounding: the bar
+        # follows what a 1e-15 relative change moves the oracle by (1.3e-11 at 502,
+        # where plain numpy with the solver's table is 1.6e-11 from the oracle)
+        moved = f * (1 + 1e-15 * W.rng(1).standard_normal(f.shape))
+        bar = max(bar, 4 * rel_l2(fc_derivative_lines(moved, d, C, 1.7, order), ref))
+    else:
+        op = FCGram(nz, d, 15, 1.7)
+        op.Mr, op.Ml = a, a[::-1, ::-1].copy()
+        op.C, op.np_, op.lzp = C, npr, npr * op.dz
+        lbar = np.where(2 * np.arange(npr) < npr, np.arange(npr), np.arange(npr) - npr)
+        op.kz = 2 * np.pi * lbar / op.lzp
+        op.kz_odd = op.kz.copy()
+        op.kz_odd[npr // 2] = 0.0
+        ref = op.derivative(f.T, order).T
+    got = s.fc_derivative(torch.from_numpy(f), order)
+    torch.cuda.synchronize()
+    assert rel_l2(got, ref) < bar
+    s.close()
