@@ -231,8 +231,9 @@ fcns_status fcns_set_z_fused(fcns_ctx* ctx, int32_t on);
  * forward transform of the nonlinear term): planes = 0 over whole arrays
  * (the default), planes > 0 slab by slab in z, that many planes at a time,
  * so that each slab's intermediate arrays are read back soon after they
- * are written (fcns_autotune picks the faster).  Results are bitwise the
- * same.  EINVAL if planes < 0 or 4 planes > 3 nz. */
+ * are written (fcns_autotune picks the faster).  Planes of 32 or 64 by 32 or
+ * 64 points pass through the three in one launch, which has no such arrays.
+ * Results are bitwise the same.  EINVAL if planes < 0 or 4 planes > 3 nz. */
 fcns_status fcns_set_slab(fcns_ctx* ctx, int32_t planes);
 
 /* Choose the layout of rk_step's (kx, y) intermediate arrays (Sec. 4.2: v
@@ -286,7 +287,9 @@ fcns_status fcns_get_wall_grad(fcns_ctx* ctx, double* out);
 /* Kernel timing for tracing and roofline reports.  While enabled, every
  * kernel that rk_step launches is bracketed by HIP events recorded on the
  * context stream (small extra launch latency).  Classes: y_back_dy,
- * y_back_dz, x_nl, y_fwd, z_stageA, z_stageB, z_back. */
+ * y_back_dz, x_nl, y_fwd, z_stageA, z_stageB, z_back, z_pass, xy_slabs.  The
+ * one launch of small planes counts once in each of the first four, its time
+ * divided by the transforms they stand for (2 : 1 : 4 : 1). */
 fcns_status fcns_set_timing(fcns_ctx* ctx, int32_t enable);
 /* The same for a subset: bit i of mask enables class i (in the order above;
  * 0 disables timing).  Bits beyond the last class: FCNS_EINVAL.  Fewer

@@ -10,7 +10,7 @@ import sys
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libfcns.so")
-SOURCES = ["zpass.hip", "zwave.hip", "xypass.hip", "xrows.hip", "lines.hip", "diag.hip", "noalloc.hip",
+SOURCES = ["zpass.hip", "zwave.hip", "xypass.hip", "xrows.hip", "plane.hip", "lines.hip", "diag.hip", "noalloc.hip",
            "fcns_api.cpp", "fcns_server.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

@@ -105,6 +105,12 @@ enum { T_YBACK_DY = 0, T_YBACK_DZ, T_XNL, T_YFWD, T_ZSTAGEA, T_ZSTAGEB, T_ZBACK,
 static const char* kTimingNames[T_NCLS] = {"y_back_dy", "y_back_dz", "x_nl", "y_fwd",
                                            "z_stageA", "z_stageB", "z_back", "z_pass",
                                            "xy_slabs"};
+// The launch of small planes does the work of the four y and x classes: its time
+// is divided among them by the one-dimensional transforms each stands for (of
+// eight per field), and counts as a launch of each.
+enum { T_PLANE = T_NCLS };
+static const int kPlaneShare[4] = {2, 1, 4, 1};   // y_back_dy, y_back_dz, x_nl, y_fwd
+static const uint32_t kPlaneMask = 1u << T_YBACK_DY | 1u << T_YBACK_DZ | 1u << T_XNL | 1u << T_YFWD;
 
 static void timing_flush(fcns_ctx* c) {
   if (c->recs.empty()) return;
@@ -112,6 +118,14 @@ static void timing_flush(fcns_ctx* c) {
   for (const auto& r : c->recs) {
     float ms = 0.f;
     if (hipEventElapsedTime(&ms, r.a, r.b) == hipSuccess) {
+      if (r.cls == T_PLANE) {
+        for (int k = 0; k < 4; ++k)
+          if ((c->tmask >> k) & 1u) {
+            c->tms[k] += ms * kPlaneShare[k] / 8;
+            c->tcnt[k] += 1;
+          }
+        continue;
+      }
       c->tms[r.cls] += ms;
       c->tcnt[r.cls] += 1;
     }
@@ -122,7 +136,7 @@ static void timing_flush(fcns_ctx* c) {
 
 static void tbeg(fcns_ctx* c, int cls) {
   c->cur.cls = -1;
-  if (!c->timing || !((c->tmask >> cls) & 1u)) return;
+  if (!c->timing || !(c->tmask & (cls == T_PLANE ? kPlaneMask : 1u << cls))) return;
   if (c->evnext + 2 > c->evpool.size()) timing_flush(c);
   c->cur.cls = cls;
   c->cur.a = c->evpool[c->evnext++];
@@ -584,6 +598,10 @@ static void mixed_to_phys(fcns_ctx* c, const cpx<double>* mixed, long long mstri
                (long long)nplanes * g.ny, nfields, c->stream);
 }
 
+// Small planes: y back, x and y forward passes in one launch, where no other
+// x pass is asked for (plane by plane, so that slabs have nothing to choose).
+static bool plane_nl(const fcns_ctx* c) { return plane_fits(xargs(c)) && c->xvar == 0; }
+
 // nonlinear term of the fields whose mixed v_f, dv_f/dz are in mv (slots 2f,
 // 2f+1) into NLB (mixed if fwd_y, else (kx, y, z)); T is the transform and
 // storage type of MV / XYB / NLB.
@@ -594,6 +612,12 @@ static void nonlinear_from_mixed(fcns_ctx* c, const cpx<T>* mv, int nfields, boo
   const bool f32 = sizeof(T) == sizeof(float);
   cpx<T>* xyb = reinterpret_cast<cpx<T>*>(c->XYB);
   cpx<T>* nlb = reinterpret_cast<cpx<T>*>(c->NLB);
+  if (fwd_y && plane_nl(c)) {
+    tbeg(c, T_PLANE);
+    launch_plane_nl<T>(xargs(c, f32), g.kys, mv, nlb, M, g.nz, nfields, c->stream);
+    tend(c);
+    return;
+  }
   // y back transforms into XYB (blocked when the x pass reads that layout)
   XArgs xa = xargs(c, f32);
   xa.blk_in = (c->xyblk && x_reads_blocked(xa)) ? 1 : 0;
@@ -1112,8 +1136,12 @@ extern "C" fcns_status fcns_autotune(fcns_ctx* c, char* report, int32_t report_l
              bpf0 ? " no-prefetch" : "", bl0, best0, bg1, bpf1 ? " no-prefetch" : "", bl1, best1);
     rep += line;
   }
-  // x pass with products: kernel variant (inputs: the y pass just run)
-  {
+  // x pass with products: kernel variant (inputs: the y pass just run); small
+  // planes take the one launch instead, which is faster than any of these
+  if (plane_fits(xargs(c))) {
+    c->xvar = 0;
+    rep += "x: variant 0 (whole planes); ";
+  } else {
     float best = 1e30f;
     int bv = 0;
     for (int v : {0, 1, 2, 3}) {
@@ -1146,7 +1174,7 @@ extern "C" fcns_status fcns_autotune(fcns_ctx* c, char* report, int32_t report_l
     for (int blk : {0, 1}) {
       if (blk && !x_reads_blocked(xargs(c))) continue;
       for (int sl : {0, 16, 32, 48, 64, 96, 128}) {
-        if (sl > 0 && (sl >= g.nz || 4 * sl > 3 * g.nz)) continue;
+        if (sl > 0 && (sl >= g.nz || 4 * sl > 3 * g.nz || plane_nl(c))) continue;
         c->slab = sl;
         c->xyblk = blk != 0;
         const float ms = time_ms(c, [&] {

@@ -196,6 +196,12 @@ void launch_x_c2r(const XArgs& a, bool big, const cpx<double>* xy, double* phys,
 template <typename T>
 void launch_x_nl(const XArgs& a, bool big, const cpx<T>* xyb, cpx<T>* nl, long long fstride,
                  long long nrows, int nfields, hipStream_t st);
+// y back transforms, x pass with products and y forward transform in one launch,
+// for nx and ny of 32 or 64 (plane.hip): mv slots 2f, 2f + 1 -> mixed nl
+bool plane_fits(const XArgs& a);
+template <typename T>
+void launch_plane_nl(const XArgs& a, double kys, const cpx<T>* mv, cpx<T>* nl, long long fstride,
+                     int nz, int nfields, hipStream_t st);
 // the x pass with products can read xyb in the blocked layout (a.blk_in)
 bool x_reads_blocked(const XArgs& a);
 

@@ -76,11 +76,11 @@ __device__ __forceinline__ int xw_nat(int i) { return i + (i >> 3); }
 // h = L mod 3.  N = 32: tw[a - 1][t] = w32^(t a).
 constexpr int XW_TW = 15 * 64;
 
-template <typename T, int N>
+template <typename T, int N, int NT = 64 * XW_WAVES>   // NT threads
 __device__ __forceinline__ void xw_twiddles(cpx<T>* tw, int tid) {
-  constexpr int S = N / 8, NTW = (N == 512 ? 15 : 14) * S;
+  constexpr int S = N / 8, NTW = (N == 512 ? 15 : N <= 64 ? 7 : 14) * S;
   static_assert(NTW <= XW_TW, "twiddle table");
-  for (int e = tid; e < NTW; e += 64 * XW_WAVES) {
+  for (int e = tid; e < NTW; e += NT) {
     const int reg = e / S, t = e % S;
     int j;  // power of wN
     if (N == 512)
