@@ -58,6 +58,18 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// A place in an LDS array, kept as the array and one index: where direct loads are
+// in flight into another array, an access through a longer chain of pointers is
+// no longer known to be of this one, and would wait for them.
+template <typename T>
+struct XwBuf {
+  cpx<T>* base;
+  int o;
+  __device__ __forceinline__ XwBuf operator+(int i) const { return {base, o + i}; }
+  __device__ __forceinline__ cpx<T>& operator[](int i) const { return base[o + i]; }
+  __device__ __forceinline__ operator cpx<T>*() const { return base + o; }
+};
+
 // Padded slots, written with the per-lane part separate so that the
 // per-register part is an instruction offset.  N = 512: element
 // 64 n0 + 8 k0 + n1 of exchange 1 sits at 65 n0 + 8 k0 + n1, element
@@ -99,8 +111,8 @@ __device__ __forceinline__ void xw_twiddles(cpx<T>* tw, int tid) {
   }
 }
 
-template <typename T>
-__device__ __forceinline__ void wave_fft512(cpx<T> (&r)[8], cpx<T>* __restrict__ buf,
+template <typename T, typename B>
+__device__ __forceinline__ void wave_fft512(cpx<T> (&r)[8], B buf,
                                             const cpx<T>* __restrict__ tw, int lane) {
   const int n0 = lane & 7, hi = lane >> 3;  // hi = n1 before, k0 after exchange 1
   Codelet<T, 8>::run(r, nullptr);
@@ -128,8 +140,8 @@ __device__ __forceinline__ void wave_fft512(cpx<T> (&r)[8], cpx<T>* __restrict__
   Codelet<T, 8>::run(r, nullptr);
 }
 
-template <typename T>
-__device__ __forceinline__ void wave_fft256(cpx<T> (&r)[8], cpx<T>* __restrict__ buf,
+template <typename T, typename B>
+__device__ __forceinline__ void wave_fft256(cpx<T> (&r)[8], B buf,
                                             const cpx<T>* __restrict__ tw, int t) {
   Codelet<T, 8>::run(r, nullptr);
 #pragma unroll
@@ -164,8 +176,8 @@ __device__ __forceinline__ void wave_fft256(cpx<T> (&r)[8], cpx<T>* __restrict__
   for (int m = 0; m < 8; ++m) r[m] = q[4 * (m & 1) + (m >> 1)];
 }
 
-template <typename T>
-__device__ __forceinline__ void wave_fft128(cpx<T> (&r)[8], cpx<T>* __restrict__ buf,
+template <typename T, typename B>
+__device__ __forceinline__ void wave_fft128(cpx<T> (&r)[8], B buf,
                                             const cpx<T>* __restrict__ tw, int t) {
   Codelet<T, 8>::run(r, nullptr);
 #pragma unroll
@@ -199,8 +211,8 @@ __device__ __forceinline__ void wave_fft128(cpx<T> (&r)[8], cpx<T>* __restrict__
   wave_sync();
 }
 
-template <typename T>
-__device__ __forceinline__ void wave_fft64(cpx<T> (&r)[8], cpx<T>* __restrict__ buf,
+template <typename T, typename B>
+__device__ __forceinline__ void wave_fft64(cpx<T> (&r)[8], B buf,
                                            const cpx<T>* __restrict__ tw, int t) {
   Codelet<T, 8>::run(r, nullptr);
 #pragma unroll
@@ -221,8 +233,8 @@ __device__ __forceinline__ void wave_fft64(cpx<T> (&r)[8], cpx<T>* __restrict__ 
 // PS h + b, b = a + 8 j < Q = 8 S / 3; lane t takes the radix-3 DFTs over h
 // of b = t, t + S, ... (< Q), X[b + Q c] for c = 0, 1, 2, writes them in
 // natural order (slots xw_nat), and reads back its own X[t + S m].
-template <typename T, int S, int PS>
-__device__ __forceinline__ void xw_radix3_out(cpx<T> (&r)[8], cpx<T>* __restrict__ buf,
+template <typename T, int S, int PS, typename B>
+__device__ __forceinline__ void xw_radix3_out(cpx<T> (&r)[8], B buf,
                                               int t) {
   constexpr int Q = 8 * S / 3;          // radix-3 DFTs per row (64 at 192, 32 at 96)
   constexpr int NB = (Q + S - 1) / S;   // per lane, the last one partial
@@ -255,8 +267,8 @@ __device__ __forceinline__ void xw_radix3_out(cpx<T> (&r)[8], cpx<T>* __restrict
   for (int m = 0; m < 8; ++m) r[m] = buf[xw_nat(t + S * m)];
 }
 
-template <typename T>
-__device__ __forceinline__ void wave_fft192(cpx<T> (&r)[8], cpx<T>* __restrict__ buf,
+template <typename T, typename B>
+__device__ __forceinline__ void wave_fft192(cpx<T> (&r)[8], B buf,
                                             const cpx<T>* __restrict__ tw, int t) {
   Codelet<T, 8>::run(r, nullptr);
 #pragma unroll
@@ -283,8 +295,8 @@ __device__ __forceinline__ void wave_fft192(cpx<T> (&r)[8], cpx<T>* __restrict__
   wave_sync();
 }
 
-template <typename T>
-__device__ __forceinline__ void wave_fft96(cpx<T> (&r)[8], cpx<T>* __restrict__ buf,
+template <typename T, typename B>
+__device__ __forceinline__ void wave_fft96(cpx<T> (&r)[8], B buf,
                                            const cpx<T>* __restrict__ tw, int t) {
   Codelet<T, 8>::run(r, nullptr);
 #pragma unroll
@@ -323,8 +335,8 @@ __device__ __forceinline__ void wave_fft96(cpx<T> (&r)[8], cpx<T>* __restrict__ 
   wave_sync();
 }
 
-template <typename T>
-__device__ __forceinline__ void wave_fft32(cpx<T> (&r)[8], cpx<T>* __restrict__ buf,
+template <typename T, typename B>
+__device__ __forceinline__ void wave_fft32(cpx<T> (&r)[8], B buf,
                                            const cpx<T>* __restrict__ tw, int t) {
   Codelet<T, 8>::run(r, nullptr);
 #pragma unroll
@@ -353,8 +365,8 @@ __device__ __forceinline__ void wave_fft32(cpx<T> (&r)[8], cpx<T>* __restrict__ 
   wave_sync();
 }
 
-template <typename T, int N>
-__device__ __forceinline__ void wave_fft(cpx<T> (&r)[8], cpx<T>* __restrict__ buf,
+template <typename T, int N, typename B>
+__device__ __forceinline__ void wave_fft(cpx<T> (&r)[8], B buf,
                                          const cpx<T>* __restrict__ tw, int t) {
   if constexpr (N == 512)
     wave_fft512<T>(r, buf, tw, t);

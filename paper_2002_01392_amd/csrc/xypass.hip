@@ -479,8 +479,8 @@ __global__ __launch_bounds__(X3_NT) void k_x_nl3(XArgs a, const cpx<T>* __restri
 // Forward transform of two finished real fields (b: none when !two), unpacked
 // into the r2c spectra of rows `row` of fields fa and fa + 1; nothing is
 // stored for a row past the end (valid false).
-template <typename T, int N>
-__device__ __forceinline__ void xw_forward(cpx<T> (&z)[8], cpx<T>* __restrict__ buf,
+template <typename T, int N, typename B>
+__device__ __forceinline__ void xw_forward(cpx<T> (&z)[8], B buf,
                                            const cpx<T>* __restrict__ tw, int t,
                                            cpx<T>* __restrict__ nl, long long fs, long long row,
                                            int nkxp, int fa, bool two, bool valid) {
@@ -524,10 +524,10 @@ __device__ __forceinline__ int xw_col_off(int kk, int ny, bool blk) {
 // value slots are read twice), and the forward transform of a pair of
 // finished fields as soon as both are complete.  Used for three fields at
 // 512 points, where the one-read schedule below needs more registers than
-// two waves per SIMD allow, and at 192, where it spills more (three fields
-// elsewhere: the one-read schedule, 7% faster at 256 and 9% at 128).
+// two waves per SIMD allow (three fields elsewhere: the one-read schedule, 7%
+// faster at 256 and 9% at 128).
 template <typename T, int NF, int N, bool BLK>
-__global__ __launch_bounds__(64 * XW_WAVES, (N == 192 || N == 96 || N == 32) ? 2 : 1) void k_x_nlw_q(XArgs a, const cpx<T>* __restrict__ xyb,
+__global__ __launch_bounds__(64 * XW_WAVES) void k_x_nlw_q(XArgs a, const cpx<T>* __restrict__ xyb,
                                                            cpx<T>* __restrict__ nl, long long fs,
                                                            long long nrows) {
   constexpr int NQ = 3 + 3 * NF, NP = (NQ + 1) / 2;
@@ -636,10 +636,23 @@ __global__ __launch_bounds__(64 * XW_WAVES, (N == 192 || N == 96 || N == 32) ? 2
   }
 }
 
-// (two waves per SIMD asked for explicitly at N = 192, 128 and 96, where the
-// compiler would otherwise go past 256 registers)
+// Does the pair's next input land in LDS by direct loads while it is transformed?
+// Bound by LDS bandwidth (some 60 16-byte accesses per lane and transform) and, at
+// two waves per SIMD, by the wait for each pair's rows; a direct load also fetches
+// a coefficient once, not once more for its mirror.  192 x 192 x 193 x pass with four
+// fields 0.351 -> 0.321 ms, three 0.294 -> 0.252, mixed 0.241 -> 0.198; 128: 0.087 ->
+// 0.081, 0.0645 -> 0.062; 256 x 256 x 257, three fields 0.374 -> 0.360, mixed 0.232 ->
+// 0.207.  Not 256 with four FP64 fields (0.482 -> 0.490: no registers left), 96 (0.037
+// -> 0.041), and 512, where a second workgroup's buffers would not fit.
+template <typename T, int NF, int N>
+constexpr bool x_direct() {
+  return N == 192 || N == 128 || (N == 256 && (NF == 3 || sizeof(T) == 4));
+}
+
+// (two waves per SIMD asked for explicitly where the compiler would otherwise go past
+// 256 registers)
 template <typename T, int NF, int N, bool BLK>
-__global__ __launch_bounds__(64 * XW_WAVES, (N == 192 || N == 128 || N == 96) ? 2 : 1) void k_x_nlw(XArgs a, const cpx<T>* __restrict__ xyb,
+__global__ __launch_bounds__(64 * XW_WAVES, (N == 192 || N == 128 || N == 96 || x_direct<T, NF, N>()) ? 2 : 1) void k_x_nlw(XArgs a, const cpx<T>* __restrict__ xyb,
                                                          cpx<T>* __restrict__ nl, long long fs,
                                                          long long nrows) {
   // Three or four fields: pairs of real quantities per complex transform,
@@ -653,8 +666,13 @@ __global__ __launch_bounds__(64 * XW_WAVES, (N == 192 || N == 128 || N == 96) ? 
   constexpr int NP = NF == 4 ? 8 : 6;
   constexpr int TH = NF - 1;  // theta's accumulator (four fields)
   constexpr int S = N / 8, RPW = 64 / S;  // lanes per row, rows per wave
-  __shared__ cpx<T> tw[XW_TW];
-  __shared__ cpx<T> xbuf[XW_WAVES][XW_BUF];
+  constexpr bool DMA = x_direct<T, NF, N>();
+  constexpr int EPL = 16 / sizeof(cpx<T>);                   // elements per direct load
+  constexpr int NI = (RPW * N / 2 / EPL + 63) / 64;          // direct loads per slot
+  constexpr int PB = 64 * EPL * NI;                          // elements of one slot
+  __shared__ cpx<T> tw[N == 512 ? XW_TW : (N <= 64 ? 7 : 14) * S];
+  __shared__ cpx<T> xbuf[XW_WAVES * XW_BUF];
+  __shared__ cpx<T> pre[DMA ? XW_WAVES : 1][DMA ? 2 * PB + 64 * EPL : 1];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
   xw_twiddles<T, N>(tw, tid);
@@ -663,7 +681,7 @@ __global__ __launch_bounds__(64 * XW_WAVES, (N == 192 || N == 128 || N == 96) ? 
   const bool spare = lane >= S * RPW;
   const int ln = spare ? lane - S : lane;
   const int t = ln % S, half = ln / S;
-  cpx<T>* buf = xbuf[wv] + half * (XW_BUF / RPW);
+  const XwBuf<T> buf{xbuf, wv * XW_BUF + half * (XW_BUF / RPW)};
   const int nkxp = a.nkxp;
   const T kxs = (T)a.kxs;
   const T sc = T(1) / T(N);
@@ -676,8 +694,48 @@ __global__ __launch_bounds__(64 * XW_WAVES, (N == 192 || N == 128 || N == 96) ? 
     const int k = t + S * m;
     xo[m] = xw_col_off(k <= N / 2 ? k : N - k, a.ny, blk);
   }
-  for (long long rw = (long long)blockIdx.x * XW_WAVES + wv; rw * RPW < nrows;
-       rw += (long long)gridDim.x * XW_WAVES) {
+  // slots of pair p: A, and B: the x derivative of A (p < 3), another slot, or none
+  auto slot_a = [](int p) { return p < 3 ? 3 * p : p < 6 ? 3 * (p - 3) + 1 : (p == 6 ? 9 : 11); };
+  auto slot_b = [](int p) { return p < 6 ? 3 * (p - 3) + 2 : 10; };
+  // direct loads of pair p of the rows whose offsets are in off, offn: k < N/2 of
+  // the wave's rows in order, then the Nyquist columns of A and B
+  unsigned off[NI], offn = 0;
+  auto offsets = [&](long long rw) {
+    auto at = [&](int r, int k) {
+      const long long row = rw * RPW + r;
+      return (unsigned)(xw_row_base(row < nrows ? row : nrows - 1, a.ny, nkxp, blk) +
+                        xw_col_off(k, a.ny, blk));
+    };
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int e = (64 * i + lane) * EPL, v = e < RPW * N / 2 ? e : 0;
+      off[i] = at(v / (N / 2), v % (N / 2));
+    }
+    offn = at(lane % RPW, N / 2);
+  };
+  auto issue = [&](int p) {
+    const bool two = p >= 3 && p < 7;
+    const cpx<T>* pa = xyb + slot_a(p) * fs;
+    const cpx<T>* pb = two ? xyb + slot_b(p) * fs : pa;
+    auto load = [&](const cpx<T>* g, cpx<T>* l) {
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
+                                       (__attribute__((address_space(3))) void*)l, 16, 0, 0);
+    };
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      load(pa + off[i], pre[wv] + 64 * EPL * i);
+      if (two) load(pb + off[i], pre[wv] + PB + 64 * EPL * i);
+    }
+    load((lane / RPW == 1 ? pb : pa) + offn, pre[wv] + 2 * PB);
+  };
+  const long long rw0 = (long long)blockIdx.x * XW_WAVES + wv;
+  if constexpr (DMA) {
+    if (rw0 * RPW < nrows) {
+      offsets(rw0);
+      issue(0);
+    }
+  }
+  for (long long rw = rw0; rw * RPW < nrows; rw += (long long)gridDim.x * XW_WAVES) {
     // a row past the end (in the last wave) computes on a copy of the last
     // row and stores nothing; spare lanes compute what their twin lanes do
     const long long row0 = rw * RPW + half;
@@ -691,23 +749,32 @@ __global__ __launch_bounds__(64 * XW_WAVES, (N == 192 || N == 128 || N == 96) ? 
       // keep each pair's loads next to its transform (hoisting them all would
       // multiply the live registers)
       __builtin_amdgcn_sched_barrier(0);
-      // slot of A; B: the x derivative of A (p < 3), another slot, or none
-      const int slotA = p < 3 ? 3 * p : p < 6 ? 3 * (p - 3) + 1 : (p == 6 ? 9 : 11);
       const bool dxA = p == 6;
       const bool sameB = p < 3;
       const bool hasB = p < 7;
-      const int slotB = p < 3 ? slotA : p < 6 ? 3 * (p - 3) + 2 : 10;
-      const long long rb = xw_row_base(row, a.ny, nkxp, blk);
-      const cpx<T>* pa = xyb + slotA * fs + rb;
-      const cpx<T>* pb = xyb + slotB * fs + rb;
+      const long long rb = DMA ? 0 : xw_row_base(row, a.ny, nkxp, blk);
+      const cpx<T>* pa = xyb + slot_a(p) * fs + rb;
+      const cpx<T>* pb = xyb + slot_b(p) * fs + rb;
+      if constexpr (DMA) __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): pair p is there
       cpx<T> r[8];
 #pragma unroll
       for (int m = 0; m < 8; ++m) {
         const int k = t + S * m;
         const int kk = k <= N / 2 ? k : N - k;
         const T kx = (kk == N / 2) ? T(0) : kxs * (T)kk;
-        cpx<T> A = pa[xo[m]];
-        cpx<T> B = sameB ? mul_i(A) * kx : (hasB ? pb[xo[m]] : zero<T>());
+        cpx<T> A, B = zero<T>();
+        if constexpr (DMA) {
+          // (m = 4: the lane of index 0 holds the Nyquist column)
+          const cpx<T>* at = pre[wv] + half * (N / 2) + (m < 4 ? k : N - k);
+          const cpx<T>* an = pre[wv] + 2 * PB + half * EPL;
+          const bool nyq = m == 4 && t == 0;
+          A = *(nyq ? an : at);
+          if (hasB && !sameB) B = *(nyq ? an + RPW * EPL : at + PB);
+        } else {
+          A = pa[xo[m]];
+          if (hasB && !sameB) B = pb[xo[m]];
+        }
+        if (sameB) B = mul_i(A) * kx;
         if (dxA) A = mul_i(A) * kx;
         if (kk == 0 || kk == N / 2) {
           A.y = T(0);
@@ -716,6 +783,20 @@ __global__ __launch_bounds__(64 * XW_WAVES, (N == 192 || N == 128 || N == 96) ? 
         // Z[k] = A + i B (k <= N/2), conj(A) + i conj(B) (k > N/2); inverse via conj
         const cpx<T> Z = (k <= N / 2) ? mk(A.x - B.y, A.y + B.x) : mk(A.x + B.y, B.x - A.y);
         r[m] = conj(Z);
+      }
+      if constexpr (DMA) {
+        // the next pair lands during this one's transform, behind its last reads
+        __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
+        __builtin_amdgcn_sched_barrier(0);
+        if (p + 1 < NP) {
+          issue(p + 1);
+        } else {
+          const long long next = rw + (long long)gridDim.x * XW_WAVES;
+          if (next * RPW < nrows) {
+            offsets(next);
+            issue(0);
+          }
+        }
       }
       wave_fft<T, N>(r, buf, tw, t);
 #pragma unroll
@@ -932,7 +1013,7 @@ void launch_x_nl(const XArgs& a, bool big, const cpx<T>* xyb, cpx<T>* nl, long l
     else if (a.nx == 192 && nfields == 4)
       FCNS_XW(k_x_nlw, 4, 192);
     else if (a.nx == 192)
-      FCNS_XW(k_x_nlw_q, 3, 192);
+      FCNS_XW(k_x_nlw, 3, 192);
     else if (a.nx == 128 && nfields == 4)
       FCNS_XW(k_x_nlw, 4, 128);
     else if (a.nx == 128)

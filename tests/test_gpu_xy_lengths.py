@@ -87,3 +87,31 @@ def test_mixed_precision_step(fcns, nx, ny):
     rv, rth, _ = o.get_state()
     assert rel_l2(v, rv) < 2e-6 and rel_l2(th, rth) < 2e-6
     s.close()
+
+
+# rows loaded ahead into LDS: several rounds of rows per workgroup with a partial
+# last one, against the tiled kernel of any length
+@pytest.mark.parametrize("nx,ny,nz,theta,precision", [
+    (128, 512, 131, True, "fp64"), (192, 258, 131, False, "fp64"), (192, 258, 131, True, "mixed"),
+    (256, 258, 131, False, "fp64"), (256, 258, 131, True, "mixed"), (128, 6, 11, False, "mixed")])
+def test_rows_loaded_ahead(fcns, nx, ny, nz, theta, precision):
+    C = 15
+    out = []
+    gen = torch.Generator(device="cuda").manual_seed(nx)
+    v = torch.randn(3, nz, ny, nx, dtype=torch.float64, device="cuda", generator=gen)
+    th = torch.randn(nz, ny, nx, dtype=torch.float64, device="cuda", generator=gen)
+    for xvar in (0, 1):
+        s = fcns.Solver(nx, ny, nz, 2.0, 3.0, 1.3, 1e-5, C=C, boussinesq=theta, kappa=1e-5,
+                        gamma=1.0, precision=precision, rk_order=1)
+        s.set_choices(f"xvar={xvar}")
+        s.set_state(v, th if theta else None)
+        s.rk_step(1e-4, 1)
+        out.append([x for x in s.get_state()[:2] if x is not None])
+        s.synchronize()
+        s.close()
+    for a, b in zip(*out):
+        assert bool(torch.isfinite(a).all())
+        # one step moves the state by dt times the term: FP64 rounding, or FP32's in
+        # the term (white noise in a step: up to 1e-1 of the state), 1e-7 of that
+        d = float(torch.linalg.vector_norm(a - b) / torch.linalg.vector_norm(b))
+        assert d < (1e-12 if precision == "fp64" else 2e-6), (nx, precision, d)
