@@ -236,7 +236,7 @@ static bool make_plan_order(int n, const std::vector<int>& rs, FFTPlan& pl, bool
   return true;
 }
 
-// The cosines and sines of the plan's stages of primes above 7 (prime_columns),
+// The cosines and sines of the plan's stages of primes above 7 (prime_matrix),
 // and each stage's place in them.
 static std::vector<double> prime_tables(FFTPlan& pl) {
   std::vector<double> t;
@@ -246,14 +246,14 @@ static std::vector<double> prime_tables(FFTPlan& pl) {
     pl.poff[s] = -1;
     if (R <= 8 || R % 2 == 0 || R > PRIME_MAX) continue;
     pl.poff[s] = (int)t.size();
-    const int H = (R - 1) / 2, kb = prime_kb(R), ld = prime_ld(R);
-    for (int g = 0; g < prime_groups(R); ++g)
-      for (int q = 1; q <= H; ++q)
+    const int H = (R - 1) / 2;
+    for (int rt = 0; rt < prime_tiles(R); ++rt)
+      for (int kk = 0; kk < prime_steps(R); ++kk)
         for (int sn = 0; sn < 2; ++sn)
-          for (int i = 0; i < ld; ++i) {
-            const int k = 1 + g * kb + i;
+          for (int lane = 0; lane < 64; ++lane) {
+            const int k = 16 * rt + lane % 16, q = 1 + 4 * kk + lane / 16;
             const long double a = 2.0L * pi * (long double)((long long)q * k % R) / R;
-            t.push_back(i < kb && k <= H ? (double)(sn ? sinl(a) : cosl(a)) : 0.0);
+            t.push_back(k <= H && q <= H ? (double)(sn ? sinl(a) : cosl(a)) : 0.0);
           }
   }
   return t;

@@ -37,25 +37,22 @@ struct FFTPlan {
   int toff[FFT_MAX_STAGES];  // stage twiddles [m-1][k] (ns > 1), else -1
   int coff[FFT_MAX_STAGES];  // roots of unity of odd radices, else -1
   int tsize;                 // complex entries of the whole table
-  // odd primes above 7: cosines and sines of the column form (prime_columns), in
-  // the transform's type, stage s at prime + poff[s]; null or -1: the pair form
+  // odd primes above 7: cosines and sines of the matrix form (prime_matrix), in the
+  // transform's type, stage s at prime + poff[s]; null or -1: the pair form
   const void* prime;
   int poff[FFT_MAX_STAGES];
 };
 
-// Output pairs per wavefront pass of the column form, and its table: for each
-// group of prime_kb pairs and each input pair q = 1..H (H = (R - 1) / 2) a row
-// of prime_ld cosines cos(2 pi q k / R), then as many sines.
-__host__ __device__ constexpr int prime_kb(int R) { return R <= 31 ? 4 : 7; }
-__host__ __device__ constexpr int prime_ld(int R) { return R <= 31 ? 4 : 8; }
-__host__ __device__ constexpr int prime_groups(int R) {
-  return ((R - 1) / 2 + prime_kb(R) - 1) / prime_kb(R);
-}
-// (none above PRIME_MAX: it grows with R^2, and one line's pairs then occupy the
-// pair form's threads)
+// The matrix form of a prime R, H = (R - 1) / 2: tiles of 16 outputs k = 0..H, steps
+// of 4 input pairs q = 1..H, and its table: for each tile and step the 64 lanes'
+// cos(2 pi q k / R), then their sines (lane: k = lane % 16 of the tile, q = lane / 16
+// of the step; 0 past H).  None above PRIME_MAX: it grows with R^2, and one line's
+// pairs then occupy the pair form's threads.
 constexpr int PRIME_MAX = 256;
+__host__ __device__ constexpr int prime_tiles(int R) { return ((R - 1) / 2 + 16) / 16; }
+__host__ __device__ constexpr int prime_steps(int R) { return ((R - 1) / 2 + 3) / 4; }
 __host__ __device__ constexpr int prime_table(int R) {
-  return R > PRIME_MAX ? 0 : prime_groups(R) * ((R - 1) / 2) * 2 * prime_ld(R);
+  return R > PRIME_MAX ? 0 : prime_tiles(R) * prime_steps(R) * 128;
 }
 
 // ---------------------------------------------------------------- codelets
@@ -400,66 +397,93 @@ __device__ __forceinline__ void prime_outputs(const cpx<T>* __restrict__ src,
   }
 }
 
-// The column form of the same stage: a lane is one column, the real or imaginary
-// part of one butterfly, and a wavefront forms prime_kb output pairs of 64
-// columns, so that the roots are wave-uniform and come through the scalar
-// cache.  With a_q, b_q the sums and differences of the column's inputs,
-// P_k = x_0 + sum a_q cos, Q_k = sum b_q sin; the two parts of a butterfly sit in
-// neighbouring lanes and exchange their Q:
-//   Re X_k = P_re + Q_im, Im X_k = P_im - Q_re, X_{R-k} with the signs swapped.
-// Two multiply-adds per pair and input against an LDS read of each input per
-// prime_kb pairs; the pair form reads five roots from LDS at indices stepped
-// modulo R for every twenty multiply-adds.
-template <typename T, bool PAD, int KB, int LD>
-__device__ __forceinline__ void prime_columns(const cpx<T>* __restrict__ src,
-                                              cpx<T>* __restrict__ dst, int R, int L, int es,
-                                              int ls, int nr, int ns, float rcp,
-                                              const void* __restrict__ tab, int tid, int nt) {
-  using CT = const __attribute__((address_space(4))) T;
-  const int H = (R - 1) / 2, ngrp = (H + KB - 1) / KB;
-  const int nb = L * nr, ncb = (2 * nb + 63) / 64;
-  const int lane = tid & 63, nw = nt >> 6;
+// The same stage on the matrix cores: with a_q, b_q the sums and differences of the
+// inputs q and R - q of a column, the real or imaginary part of one butterfly,
+//   P_k = x_0 + sum a_q cos(2 pi q k / R),  Q_k = sum b_q sin(2 pi q k / R),
+//   Re X_k = P_re + Q_im, Im X_k = P_im - Q_re, X_{R-k} with the signs swapped
+// (k = 0: X_0 = P_0).  A wavefront forms 16 k of 16 columns by 16 x 16 x 4 products, the
+// roots from a table through L1, the inputs from LDS once; the two parts of a
+// butterfly sit in neighbouring lanes and exchange their Q.  The pair form reads five
+// roots and two inputs from LDS for twenty multiply-adds and is bound by LDS.  Fused
+// z pass at 256 x 256 x 257 (6 x 47) 1.55 -> 1.29 ms; stage A and back transforms at
+// 160 x 160 x 161 (6 x 31) 0.406 -> 0.343 and 0.253 -> 0.209 ms, at 120 x 84 x 81 (2 x 53)
+// 0.144 -> 0.102 and 0.095 -> 0.064.
+typedef double v4d __attribute__((ext_vector_type(4)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+template <typename T>
+struct Mfma16;
+template <>
+struct Mfma16<double> {
+  using V = v4d;
+  __device__ __forceinline__ static V mac(double a, double b, V c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  // the row that element r of lanes 16 g .. 16 g + 15 holds
+  __device__ __forceinline__ static int row(int g, int r) { return 4 * r + g; }
+};
+template <>
+struct Mfma16<float> {
+  using V = v4f;
+  __device__ __forceinline__ static V mac(float a, float b, V c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  __device__ __forceinline__ static int row(int g, int r) { return 4 * g + r; }
+};
+
+template <typename T, bool PAD>
+__device__ __forceinline__ void prime_matrix(const cpx<T>* __restrict__ src,
+                                             cpx<T>* __restrict__ dst, int R, int L, int es,
+                                             int ls, int nr, int ns, float rcp,
+                                             const T* __restrict__ tab, int tid, int nt) {
+  using MF = Mfma16<T>;
+  const int H = (R - 1) / 2, nrt = prime_tiles(R), nk = prime_steps(R);
+  const int nb = L * nr, nct = (2 * nb + 15) / 16;
+  const int lane = tid & 63, c = lane & 15, g = lane >> 4, nw = nt >> 6;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const T* S0 = reinterpret_cast<const T*>(src);
   T* D0 = reinterpret_cast<T*>(dst);
-  for (int item = wv; item < ncb * ngrp; item += nw) {
-    const int grp = item / ncb, cb = item - grp * ncb;
-    const int col = cb * 64 + lane, part = col & 1;
+#pragma unroll 1
+  for (int item = wv; item < nrt * nct; item += nw) {
+    const int ct = item / nrt, rt = item - ct * nrt;
+    const int col = ct * 16 + c, part = col & 1;
     const bool ok = col < 2 * nb;
     const int b = ok ? col >> 1 : nb - 1;
     const int l = b % L, j = b / L;
     const int k = fast_mod(j, ns, rcp);
     auto S = [&](int m) -> T { return S0[2 * lds_pos<PAD>(l, j + m * nr, es, ls) + part]; };
+    const T* t = tab + rt * nk * 128 + lane;
     const T x0 = S(0);
-    T sum = x0, P[KB], Q[KB];
-#pragma unroll
-    for (int i = 0; i < KB; ++i) {
-      P[i] = x0;
-      Q[i] = T(0);
-    }
-    CT* c = reinterpret_cast<CT*>(reinterpret_cast<uintptr_t>(tab)) + grp * H * 2 * LD;
-#pragma unroll 1
-    for (int q = 1; q <= H; ++q, c += 2 * LD) {
-      const T xa = S(q), xb = S(R - q);
-      const T ps = xa + xb, ms = xa - xb;
-      sum += ps;
-#pragma unroll
-      for (int i = 0; i < KB; ++i) {
-        P[i] += ps * c[i];
-        Q[i] += ms * c[LD + i];
+    typename MF::V P = {x0, x0, x0, x0}, Q = {T(0), T(0), T(0), T(0)};
+    // (the next step's roots and inputs are on their way during this one's products)
+    auto pair = [&](int kk, T& xa, T& xb) {
+      const int q1 = 1 + 4 * kk + g, q = q1 <= H ? q1 : H;   // (past H the roots are 0)
+      xa = S(q);
+      xb = S(R - q);
+    };
+    T cs = t[0], sn = t[64], xa, xb;
+    pair(0, xa, xb);
+#pragma unroll 2
+    for (int kk = 0; kk < nk; ++kk) {
+      const T c0 = cs, s0 = sn, a0 = xa + xb, b0 = xa - xb;
+      if (kk + 1 < nk) {
+        t += 128;
+        cs = t[0];
+        sn = t[64];
+        pair(kk + 1, xa, xb);
       }
+      P = MF::mac(c0, a0, P);
+      Q = MF::mac(s0, b0, Q);
     }
     const int o = (j - k) * R + k;
     auto D = [&](int m) -> T& { return D0[2 * lds_pos<PAD>(l, o + m * ns, es, ls) + part]; };
-    if (ok && grp == 0) D(0) = sum;
     const T sg = part ? T(-1) : T(1);
 #pragma unroll
-    for (int i = 0; i < KB; ++i) {
-      const T qo = sg * lane_xor1(Q[i]);
-      const int kk = 1 + grp * KB + i;
+    for (int r = 0; r < 4; ++r) {
+      const T qo = sg * lane_xor1(Q[r]);
+      const int kk = rt * 16 + MF::row(g, r);
       if (ok && kk <= H) {
-        D(kk) = P[i] + qo;
-        D(R - kk) = P[i] - qo;
+        D(kk) = P[r] + qo;
+        if (kk) D(R - kk) = P[r] - qo;
       }
     }
   }
@@ -467,9 +491,9 @@ __device__ __forceinline__ void prime_columns(const cpx<T>* __restrict__ src,
 
 constexpr int PRIME_PG = 5;
 
-// COLS: the plan surely has its prime table (compiled plans); a run-time plan
+// TABLE: the plan surely has its prime table (compiled plans); a run-time plan
 // without one (the context-free derivative) runs the pair form.
-template <typename T, bool PAD, bool COLS>
+template <typename T, bool PAD, bool TABLE>
 __device__ __forceinline__ void fft_stage_prime(cpx<T>* __restrict__ src, cpx<T>* __restrict__ dst,
                                                 int R, int L, int es, int ls, int n, int ns,
                                                 const cpx<T>* __restrict__ tws,
@@ -488,24 +512,15 @@ __device__ __forceinline__ void fft_stage_prime(cpx<T>* __restrict__ src, cpx<T>
     }
     __syncthreads();
   }
-  // The pair form where its items fill seven eighths of the threads (6 x 47 points
-  // of 8 lines: 240 of 256; stage A 0.77 ms against 0.82 with columns at 256 x 256
-  // x 257), the column form below that (2 x 53: 96 of 256; stage A 0.144 -> 0.109
-  // ms, back transforms 0.095 -> 0.069 at 120 x 84 x 81; 6 x 31: 0.406 -> 0.364 and
-  // 0.253 -> 0.228 at 160 x 160 x 161).
-  const int H = (R - 1) / 2;
-  const bool pairs = 8 * nb * ((H + PRIME_PG - 1) / PRIME_PG) >= 7 * nt;
-  if (!pairs && (COLS || (prime && poff >= 0))) {
-    const T* tab = reinterpret_cast<const T*>(prime) + poff;
-    if (prime_kb(R) == 4)
-      prime_columns<T, PAD, 4, 4>(src, dst, R, L, es, ls, nr, ns, rcp, tab, tid, nt);
-    else
-      prime_columns<T, PAD, 7, 8>(src, dst, R, L, es, ls, nr, ns, rcp, tab, tid, nt);
+  if (TABLE || (prime && poff >= 0)) {
+    prime_matrix<T, PAD>(src, dst, R, L, es, ls, nr, ns, rcp,
+                         reinterpret_cast<const T*>(prime) + poff, tid, nt);
     return;
   }
-  if (pairs || 2 * nb * ((H + PRIME_PG - 1) / PRIME_PG) >= nt)
+  const int H = (R - 1) / 2;
+  if (2 * nb * ((H + PRIME_PG - 1) / PRIME_PG) >= nt)
     prime_outputs<T, PAD, PRIME_PG>(src, dst, R, L, es, ls, nr, ns, rcp, cw, tid, nt);
-  else if constexpr (!COLS)
+  else
     prime_outputs<T, PAD, 1>(src, dst, R, L, es, ls, nr, ns, rcp, cw, tid, nt);
 }
 
@@ -599,13 +614,67 @@ __device__ __forceinline__ void sfft_stage(const cpx<T>* __restrict__ src, cpx<T
   }
 }
 
+// Two stages R1, R2 in one pass through registers: the R1-point butterflies j + nrt a
+// (a < R2, nrt = n / (R1 R2), a multiple of ns) write what the R2-point butterflies
+// (j - k) R1 + k + m ns (m < R1) read.  Saves a pass over LDS and a barrier; the
+// arithmetic is that of the two stages.  6 x 47: fused z pass at 256 x 256 x 257
+// 1.29 -> 1.23 ms.  Not in the run-time engine, where its registers cost every other
+// length more (x pass at 120 points 0.075 -> 0.128 ms).
+template <typename T, int R1, int R2, int NS, int N, int L, int NT, bool PAD>
+__device__ __forceinline__ void sfft_stage2(const cpx<T>* __restrict__ src, cpx<T>* __restrict__ dst,
+                                            int es, int ls,
+                                            const cpx<T>* __restrict__ tws1,
+                                            const cpx<T>* __restrict__ cw1,
+                                            const cpx<T>* __restrict__ tws2,
+                                            const cpx<T>* __restrict__ cw2, int tid) {
+  constexpr int ns = NS, nrt = N / (R1 * R2), nb = L * nrt;
+#pragma unroll 1
+  for (int g = tid; g < nb; g += NT) {
+    const int l = g % L, j = g / L;
+    const int k = j % ns;
+    cpx<T> u[R2][R1], w[R2];
+#pragma unroll
+    for (int a = 0; a < R2; ++a) {
+#pragma unroll
+      for (int m = 0; m < R1; ++m)
+        u[a][m] = src[lds_pos<PAD>(l, j + nrt * (a + R2 * m), es, ls)];
+      if (ns > 1) {
+#pragma unroll
+        for (int m = 1; m < R1; ++m) u[a][m] = u[a][m] * tws1[(m - 1) * ns + k];
+      }
+      Codelet<T, R1>::run(u[a], cw1);
+    }
+    const int o = (j - k) * (R1 * R2) + k;
+#pragma unroll
+    for (int m = 0; m < R1; ++m) {
+      w[0] = u[0][m];
+#pragma unroll
+      for (int a = 1; a < R2; ++a) w[a] = u[a][m] * tws2[((a - 1) * R1 + m) * ns + k];
+      Codelet<T, R2>::run(w, cw2);
+#pragma unroll
+      for (int a = 0; a < R2; ++a)
+        dst[lds_pos<PAD>(l, o + (m + a * R1) * ns, es, ls)] = w[a];
+    }
+  }
+}
+
+template <int... Rest>
+inline constexpr bool only_3 = false;
+template <>
+inline constexpr bool only_3<3> = true;
+
 template <typename T, int L, int NT, bool PAD, int N, int S, int NS, int R, int... Rest>
 __device__ __forceinline__ cpx<T>* sfft_from(cpx<T>* src, cpx<T>* dst, int es, int ls,
                                              const FFTPlan& pl, const cpx<T>* __restrict__ tw,
                                              int tid) {
   const cpx<T>* tws = tw + (NS > 1 ? pl.toff[S] : 0);
   const cpx<T>* cw = tw + ((R & 1) ? pl.coff[S] : 0);
-  if constexpr (R % 2 == 1 && R > 8)  // odd primes: the cooperative stage, constant sizes
+  if constexpr (R == 2 && only_3<Rest...>) {
+    sfft_stage2<T, 2, 3, NS, N, L, NT, PAD>(src, dst, es, ls, tws, cw, tw + pl.toff[S + 1],
+                                            tw + pl.coff[S + 1], tid);
+    __syncthreads();
+    return dst;
+  } else if constexpr (R % 2 == 1 && R > 8)  // odd primes: the cooperative stage, constant sizes
     fft_stage_prime<T, PAD, true>(src, dst, R, L, es, ls, N, NS, tws, cw, pl.prime, pl.poff[S], tid, NT);
   else
     sfft_stage<T, R, NS, N, L, NT, PAD>(src, dst, es, ls, tws, cw, tid);

@@ -130,8 +130,9 @@ def test_fc_derivative_wavefront_lengths(fcns, npr, C, n, order):
     s.close()
 
 
-# lengths with primes above 7 (one stage of them, two, a square), both forms of the
-# prime stage: few butterflies (columns), many (pairs), and the longest line
+# lengths with primes above 7 (one stage of them, two, a square): one tile of outputs
+# (11 to 31, exactly full at 31), more (53 to 251, the longest line), columns that fill
+# their tiles and that do not
 @pytest.mark.parametrize("npr,C", [(22, 5), (26, 15), (58, 25), (62, 15), (106, 25), (154, 25),
                                    (186, 25), (218, 25), (242, 25), (254, 25), (282, 25),
                                    (286, 25), (442, 25), (502, 25)])
