@@ -863,12 +863,17 @@ template <typename T>
 void launch_y(const YArgs& a, bool big, bool inv, int mode, const cpx<T>* src, cpx<T>* dst,
               cpx<T>* dst2, long long sfs, long long dfs, int nplanes, int nfields,
               hipStream_t st) {
-  // Lines per tile: 4 or, at 512 points, 8 by choice for the compiled plans; 8
-  // over 256 threads for run-time plans up to Y_DYN8 points, whose stages of
-  // ny / radix butterflies per line would leave most threads idle with 4 lines
-  // (at 84 points 48 to 112 of 256), and whose tiles are then whole 128-byte
-  // lines (a channel solve of 32 x 32 x 33 with them: 1.64 -> 1.48 ms).  Above
-  // that two 8-line buffers would leave one workgroup per CU.
+  // Lines per tile: 4 or, at 512 points, 8 by choice; 8 over 256 threads for the
+  // shorter compiled plans and for run-time plans up to Y_DYN8 points, whose stages
+  // of ny / radix butterflies per line leave most threads idle with 4 lines (at 84
+  // points 48 to 112 of 256, at 128 64 of 256 in a radix-8 stage), and whose tiles are
+  // then whole 128-byte lines.  A channel solve of 32 x 32 x 33 with them: 1.64 -> 1.48 ms;
+  // back with d/dy, back, forward at 256 x 256 x 257 with theta 0.437, 0.280, 0.219 ->
+  // 0.382, 0.252, 0.216 ms, mixed (three fields) 0.219, 0.160, 0.125 -> 0.167, 0.132,
+  // 0.102; 128: 0.054, 0.040, 0.036 -> 0.049, 0.041, 0.033; 96: 0.027, 0.020, 0.021 ->
+  // 0.024, 0.017, 0.018.  Not 192 points in FP64: three such workgroups per CU, 0.166,
+  // 0.126, 0.093 -> 0.172, 0.124, 0.100.  Above Y_DYN8 two 8-line buffers would leave
+  // one workgroup per CU.
   const bool compiled = y_wide_tiles(a) || (a.ny == 256 && plan_is(a.pl, {8, 8, 4})) ||
                         (a.ny == 192 && plan_is(a.pl, {8, 8, 3})) ||
                         (a.ny == 128 && plan_is(a.pl, {8, 8, 2})) ||
@@ -876,16 +881,17 @@ void launch_y(const YArgs& a, bool big, bool inv, int mode, const cpx<T>* src, c
                         (a.ny == 64 && plan_is(a.pl, {8, 8}));
   constexpr int Y_DYN8 = 288;
   const bool dyn8 = !compiled && a.ny <= Y_DYN8;
-  const int L = dyn8 || (a.lines == 8 && y_wide_tiles(a)) ? 8 : YL;
+  const bool c8 = compiled && a.ny < 512 && !(a.ny == 192 && sizeof(T) == 8);
+  const int L = c8 || dyn8 || (a.lines == 8 && y_wide_tiles(a)) ? 8 : YL;
   const long long nlines = (long long)nplanes * a.nkxp;
   const long long ntiles = (nlines + L - 1) / L;
+  const size_t sh = y_lds_bytes(a.ny, a.pl.tsize, sizeof(cpx<T>), L);
   const long long yg = a.grid > 0 ? a.grid : Y_GRID;
   // fewer tiles than the persistent grid: one workgroup per tile, rounded up
   // to whole chunks of 64 so that the XCD-aware order still applies
   long long gx = ntiles < yg ? ntiles : yg;
   if (gx < yg && gx % 64) gx = std::min(yg, (gx + 63) / 64 * 64);
   dim3 grid((unsigned)gx, nfields);
-  const size_t sh = y_lds_bytes(a.ny, a.pl.tsize, sizeof(cpx<T>), L);
   const int iv = inv ? 1 : 0;
 #define FCNS_YN(FPV, OWNV, LV, NTV)                                                         \
   do {                                                                                      \
@@ -905,19 +911,22 @@ void launch_y(const YArgs& a, bool big, bool inv, int mode, const cpx<T>* src, c
       FCNS_Y(P512, 8);
   } else if (compiled && a.ny == 256) {
     using P256 = SPlan<8, 8, 4>;
-    FCNS_Y(P256, 4);
+    FCNS_YN(P256, 8, 8, 256);
   } else if (compiled && a.ny == 192) {
     using P192 = SPlan<8, 8, 3>;
-    FCNS_Y(P192, 4);
+    if constexpr (sizeof(T) == 4)
+      FCNS_YN(P192, 6, 8, 256);
+    else
+      FCNS_Y(P192, 3);
   } else if (compiled && a.ny == 128) {
     using P128 = SPlan<8, 8, 2>;
-    FCNS_Y(P128, 4);
+    FCNS_YN(P128, 4, 8, 256);
   } else if (compiled && a.ny == 96) {
     using P96 = SPlan<8, 4, 3>;
-    FCNS_Y(P96, 4);
+    FCNS_YN(P96, 3, 8, 256);
   } else if (compiled) {
     using P64 = SPlan<8, 8>;
-    FCNS_Y(P64, 4);
+    FCNS_YN(P64, 2, 8, 256);
   } else if (dyn8) {
     if (big) {
       if (a.ny <= 128) FCNS_YN(DynPlan<true>, 4, 8, 256);

@@ -115,3 +115,16 @@ def test_rows_loaded_ahead(fcns, nx, ny, nz, theta, precision):
         # the term (white noise in a step: up to 1e-1 of the state), 1e-7 of that
         d = float(torch.linalg.vector_norm(a - b) / torch.linalg.vector_norm(b))
         assert d < (1e-12 if precision == "fp64" else 2e-6), (nx, precision, d)
+
+
+# compiled y plans: tiles of 8 columns that end inside a plane or span two
+@pytest.mark.parametrize("nx,ny,theta", [(4, 64, True), (10, 64, False), (6, 96, True),
+                                         (20, 128, False), (4, 128, True), (12, 192, True),
+                                         (20, 256, True)])
+def test_columns_of_compiled_plans(fcns, nx, ny, theta):
+    test_nonlinear_term_and_state(fcns, nx, ny, theta)
+
+
+@pytest.mark.parametrize("ny", [96, 192])
+def test_columns_of_compiled_plans_mixed(fcns, ny):
+    test_mixed_precision_step(fcns, 12, ny)
