@@ -247,13 +247,18 @@ static std::vector<double> prime_tables(FFTPlan& pl) {
     if (R <= 8 || R % 2 == 0 || R > PRIME_MAX) continue;
     pl.poff[s] = (int)t.size();
     const int H = (R - 1) / 2;
+    std::vector<double> c(R), sn(R);
+    for (int m = 0; m < R; ++m) {
+      const long double a = 2.0L * pi * (long double)m / R;
+      c[m] = (double)cosl(a);
+      sn[m] = (double)sinl(a);
+    }
     for (int rt = 0; rt < prime_tiles(R); ++rt)
       for (int kk = 0; kk < prime_steps(R); ++kk)
-        for (int sn = 0; sn < 2; ++sn)
+        for (const auto* f : {&c, &sn})
           for (int lane = 0; lane < 64; ++lane) {
             const int k = 16 * rt + lane % 16, q = 1 + 4 * kk + lane / 16;
-            const long double a = 2.0L * pi * (long double)((long long)q * k % R) / R;
-            t.push_back(k <= H && q <= H ? (double)(sn ? sinl(a) : cosl(a)) : 0.0);
+            t.push_back(k <= H && q <= H ? (*f)[q * k % R] : 0.0);
           }
   }
   return t;

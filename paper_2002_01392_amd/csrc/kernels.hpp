@@ -11,7 +11,7 @@ namespace fcns {
 constexpr int ZPB = 8;
 constexpr int ZNT = 256;
 constexpr int ZLS = ZNT / ZPB;  // rows a thread steps over (its pencil is tid % ZPB)
-// y kernels: YL lines (consecutive kx) per workgroup
+// y kernels: YL or 2 YL lines (consecutive kx) per workgroup (launch_y)
 constexpr int YL = 4;
 constexpr int YNT = 256;
 constexpr long long Y_GRID = 1024;  // persistent y workgroups per field
