@@ -190,7 +190,9 @@ fcns_status fcns_batch_step(fcns_ctx* const* ctxs, int32_t n, const double* dts,
  * (continuation, z transforms, RK combine, projection, back transforms) for
  * all members together, workgroup by workgroup over their pencil groups, on a
  * stream of the batch (members of N' = 32 K: one kernel per length, the
- * others one for all); each member waits for it before its next pass.  Each member's result matches its own
+ * others one for all, except that a member of N' = 288 with a table of
+ * C + d > 64 or d > 7 runs its own fused pass on its own stream); each member
+ * waits for it before its next pass.  Each member's result matches its own
  * fcns_rk_step with the fused z pass to rounding (the same per-workgroup
  * code).  The batch reads its members' parameters, tables and buffers at
  * every run (a member retuned or given new parameters is picked up).

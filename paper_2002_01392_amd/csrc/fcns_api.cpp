@@ -1423,7 +1423,8 @@ struct fcns_batch {
   std::vector<ZPassDesc> hdesc;   // the host copy they were made from
   std::vector<double> dt;         // per context
   // One launch per bucket and stage: the members of one N' = 32 K (npr), and
-  // those of any other length (npr = 0, the run-time plan engine).
+  // those of any other length (npr = 0, the run-time plan engine).  Members
+  // whose plan exists compiled only (npr = -1) run their own fused pass.
   struct Bucket {
     int npr = 0, first = 0, n = 0;
     long long groups = 0;
@@ -1434,13 +1435,18 @@ struct fcns_batch {
   std::vector<Bucket> buckets;
 };
 
+// The bucket of a member.
+static int batch_key(const fcns_ctx* c) {
+  return wave_z(c) ? c->g.npr : run_time_plan(c->plz) ? 0 : -1;
+}
+
 // The descriptors of every (stage, context) from the contexts as they are
 // now (their tables, parameters and buffers), and the launch shapes.
 static void batch_descriptors(fcns_batch* b, std::vector<ZPassDesc>& h) {
   const int n = (int)b->ctx.size(), o = b->o;
   h.resize((size_t)o * n);
   memset(h.data(), 0, h.size() * sizeof(ZPassDesc));
-  auto key = [&](int i) { return wave_z(b->ctx[i]) ? b->ctx[i]->g.npr : 0; };
+  auto key = [&](int i) { return batch_key(b->ctx[i]); };
   std::vector<int> order(n);
   for (int i = 0; i < n; ++i) order[i] = i;
   std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return key(x) < key(y); });
@@ -1552,20 +1558,21 @@ extern "C" fcns_status fcns_batch_run(fcns_batch* b, int32_t nsteps) {
         fcns_ctx* c = b->ctx[i];
         nonlinear_from_mixed<double>(c, c->MV, c->nf, true);
         cpx<double>*W, *OUT;
-        if (stage_buffers(c, j, o, true, &W, &OUT)) {
+        const bool fused = stage_buffers(c, j, o, true, &W, &OUT);
+        if (fused && batch_key(c) >= 0) {
           any = true;
           (void)hipEventRecord(b->ev_ctx[i], c->stream);
           (void)hipStreamWaitEvent(b->stream, b->ev_ctx[i], 0);
         } else {
           z_part<double>(c, W, OUT, b->dt[i] / (double)(o - j + 1),
-                         c->prob.keep_pressure && j == o, false);
+                         c->prob.keep_pressure && j == o, fused);
         }
       }
       if (!any) continue;
       for (const auto& bk : b->buckets) {
         // (a bucket's members take the fused pass at the same stages: all but the
         // only one of o = 1, and without the wavefront pass the middle ones of o >= 3)
-        if (o == 1 || (!bk.npr && j > 1 && j < o)) continue;
+        if (bk.npr < 0 || o == 1 || (!bk.npr && j > 1 && j < o)) continue;
         const ZPassDesc* d = b->desc + (size_t)(j - 1) * n + bk.first;
         if (bk.npr)
           launch_zw_pass_batch(d, bk.n, bk.groups, bk.npr, b->stream);
@@ -1575,7 +1582,7 @@ extern "C" fcns_status fcns_batch_run(fcns_batch* b, int32_t nsteps) {
       (void)hipEventRecord(b->ev_z, b->stream);
       for (int i = 0; i < n; ++i) {
         cpx<double>*W, *OUT;
-        if (stage_buffers(b->ctx[i], j, o, true, &W, &OUT))
+        if (stage_buffers(b->ctx[i], j, o, true, &W, &OUT) && batch_key(b->ctx[i]) >= 0)
           (void)hipStreamWaitEvent(b->ctx[i]->stream, b->ev_z, 0);
       }
     }

@@ -32,6 +32,14 @@ inline bool plan_is(const FFTPlan& pl, std::initializer_list<int> rs) {
   return true;
 }
 
+// Can the run-time engine run the plan?  Its even radices are 2, 4 and 8; the
+// radices 16 and 18 of the 288-point plan exist compiled only.
+inline bool run_time_plan(const FFTPlan& pl) {
+  for (int s = 0; s < pl.nst; ++s)
+    if (pl.r[s] % 2 == 0 && pl.r[s] > 8) return false;
+  return true;
+}
+
 struct ZArgs {
   Geom g;
   FFTPlan pl;             // N'-point plan (lines = ZPB, threads = ZNT)
@@ -152,8 +160,8 @@ void launch_zw_deriv(const ZArgs& a, const double* in, double* out, long long nl
 
 // One launch of the fused z pass over several problems (device array of n
 // descriptors; wg0 = first workgroup of each problem, ascending from 0;
-// groups = total workgroups).  Every problem runs the run-time plan engine
-// (big: some plan has a prime radix above 7); max_npr picks the rows per
+// groups = total workgroups).  launch_z_pass_batch runs the run-time plan engine
+// for every problem (run_time_plan; big: some plan has a prime radix above 7); max_npr picks the rows per
 // thread; lds = the largest z_pass_lds of the batch.
 struct ZPassDesc {
   ZArgs a;
