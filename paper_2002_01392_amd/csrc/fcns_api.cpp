@@ -548,10 +548,11 @@ extern "C" fcns_status fcns_footprint(const fcns_problem* p, int64_t* bytes) {
   const long long nf = p->boussinesq ? 4 : 3;
   // P, Q, VS; MV, MVT, XYB, NLB, PM; GW, GWT (complex128), plus tables
   const long long elems = 3 * nf * S + (2 * nf + 2 * nf + 3 * nf + nf + 1) * M + 8 * npen;
-  // the cosines and sines of each length's primes above 7
+  // the cosines and sines of each length's primes above 7 (none above PRIME_MAX;
+  // the lengths are the caller's, and unbounded here)
   auto primes = [&](long long n) {
     long long b = 0;
-    for (long long q = 2; n > 1; ++q)
+    for (long long q = 2; n > 1 && q <= PRIME_MAX; ++q)
       while (n % q == 0) {
         if (q > 7) b += 8LL * prime_table((int)q);
         n /= q;

@@ -73,3 +73,19 @@ def test_footprint_counts_the_context_buffers():
     W = 8 * 512 * nkxp * 16          # wall-gradient arrays
     assert 12 * S + 33 * M + W <= b < 12 * S + 33 * M + W + (1 << 22)
     assert problem_bytes(32, 32, 33, 31, 3) < problem_bytes(64, 64, 65, 31, 3)
+
+
+@pytest.mark.skipif(not os.path.exists(LIB), reason="libfcns.so not built")
+@pytest.mark.parametrize("axis", [0, 1, 2])
+def test_footprint_of_any_length_is_immediate(axis):
+    # a request's lengths reach it before any limit is checked: 2 x 1073741789 (a
+    # prime) is factored no further than the tables go
+    import time
+    from paper_2002_01392_amd import problem_bytes
+    n = [4, 4, 33]
+    n[axis] = 2 * 1073741789 - (31 if axis == 2 else 0)
+    problem_bytes(4, 4, 33, 31, 3)
+    t0 = time.perf_counter()
+    b = problem_bytes(*n, 31, 3)
+    assert time.perf_counter() - t0 < 0.5
+    assert b > 16 * (n[0] // 2) * n[1] * n[2]
