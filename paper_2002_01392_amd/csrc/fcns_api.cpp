@@ -1430,7 +1430,7 @@ struct fcns_batch {
     int npr = 0, first = 0, n = 0;
     long long groups = 0;
     int max_npr = 0;
-    bool big = false;
+    int primes = PRIMES_NONE;
     size_t lds = 0;
   };
   std::vector<Bucket> buckets;
@@ -1476,7 +1476,10 @@ static void batch_descriptors(fcns_batch* b, std::vector<ZPassDesc>& h) {
     bk.n++;
     bk.groups += z_pass_groups(a);
     bk.max_npr = std::max(bk.max_npr, c->g.npr);
-    bk.big = bk.big || c->big_z;
+    // (pairs run any plan, matrices those that all take them)
+    const int form = prime_form(a.pl, c->big_z, PF_Z);
+    if (form != PRIMES_NONE)
+      bk.primes = bk.primes == PRIMES_NONE || bk.primes == form ? form : PRIMES_PAIRS;
     bk.lds = std::max(bk.lds, z_pass_lds(a));
   }
 }
@@ -1578,7 +1581,7 @@ extern "C" fcns_status fcns_batch_run(fcns_batch* b, int32_t nsteps) {
         if (bk.npr)
           launch_zw_pass_batch(d, bk.n, bk.groups, bk.npr, b->stream);
         else
-          launch_z_pass_batch(d, bk.n, bk.groups, bk.max_npr, bk.big, bk.lds, b->stream);
+          launch_z_pass_batch(d, bk.n, bk.groups, bk.max_npr, bk.primes, bk.lds, b->stream);
       }
       (void)hipEventRecord(b->ev_z, b->stream);
       for (int i = 0; i < n; ++i) {

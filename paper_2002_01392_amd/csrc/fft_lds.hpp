@@ -369,8 +369,6 @@ __device__ __forceinline__ void prime_outputs(const cpx<T>* __restrict__ src,
       im[i] = zero<T>();
       qk[i] = 0;
     }
-    // (unrolled over a constant length this loop would spill hundreds of registers)
-#pragma unroll 1
     for (int q = 1; q <= H; ++q) {
       const cpx<T> xa = S(q), xb = S(R - q);
       const cpx<T> ps = xa + xb, ms = xa - xb;
@@ -491,9 +489,11 @@ __device__ __forceinline__ void prime_matrix(const cpx<T>* __restrict__ src,
 
 constexpr int PRIME_PG = 5;
 
-// TABLE: the plan surely has its prime table (compiled plans); a run-time plan
-// without one (the context-free derivative) runs the pair form.
-template <typename T, bool PAD, bool TABLE>
+// How a plan's primes above 7 are transformed (prime_form chooses): a kernel holds
+// one form only, as the matrix accumulators would cost the other's occupancy.
+enum { PRIMES_NONE = 0, PRIMES_PAIRS = 1, PRIMES_MATRIX = 2 };
+
+template <typename T, bool PAD, int PM>
 __device__ __forceinline__ void fft_stage_prime(cpx<T>* __restrict__ src, cpx<T>* __restrict__ dst,
                                                 int R, int L, int es, int ls, int n, int ns,
                                                 const cpx<T>* __restrict__ tws,
@@ -512,16 +512,16 @@ __device__ __forceinline__ void fft_stage_prime(cpx<T>* __restrict__ src, cpx<T>
     }
     __syncthreads();
   }
-  if (TABLE || (prime && poff >= 0)) {
+  if constexpr (PM == PRIMES_MATRIX) {
     prime_matrix<T, PAD>(src, dst, R, L, es, ls, nr, ns, rcp,
                          reinterpret_cast<const T*>(prime) + poff, tid, nt);
-    return;
+  } else {
+    const int H = (R - 1) / 2;
+    if (2 * nb * ((H + PRIME_PG - 1) / PRIME_PG) >= nt)
+      prime_outputs<T, PAD, PRIME_PG>(src, dst, R, L, es, ls, nr, ns, rcp, cw, tid, nt);
+    else
+      prime_outputs<T, PAD, 1>(src, dst, R, L, es, ls, nr, ns, rcp, cw, tid, nt);
   }
-  const int H = (R - 1) / 2;
-  if (2 * nb * ((H + PRIME_PG - 1) / PRIME_PG) >= nt)
-    prime_outputs<T, PAD, PRIME_PG>(src, dst, R, L, es, ls, nr, ns, rcp, cw, tid, nt);
-  else
-    prime_outputs<T, PAD, 1>(src, dst, R, L, es, ls, nr, ns, rcp, cw, tid, nt);
 }
 
 // ---------------------------------------------------------------- driver
@@ -529,9 +529,9 @@ __device__ __forceinline__ void fft_stage_prime(cpx<T>* __restrict__ src, cpx<T>
 // scratch of the same size; tw is the plan's twiddle table (in LDS).
 // Returns the buffer holding the result.  All threads of the workgroup must
 // call it, after a barrier that makes the input visible; it synchronises
-// before returning.  BIG: also dispatch the run-time stage for odd primes
-// above 7.  PAD: padded line layout (lds_pos).
-template <typename T, int L, bool BIG, bool PAD = false>
+// before returning.  PM: the form of odd primes above 7, if the plan has any.
+// PAD: padded line layout (lds_pos).
+template <typename T, int L, int PM, bool PAD = false>
 __device__ __forceinline__ cpx<T>* fft_fwd(cpx<T>* buf0, cpx<T>* buf1, int es, int ls,
                                            const FFTPlan& pl, const cpx<T>* __restrict__ tw,
                                            int tid, int nt) {
@@ -551,9 +551,9 @@ __device__ __forceinline__ cpx<T>* fft_fwd(cpx<T>* buf0, cpx<T>* buf1, int es, i
       case 7: fft_stage<T, 7, PAD>(src, dst, L, es, ls, n, ns, tws, cw, tid, nt); break;
       case 8: fft_stage<T, 8, PAD>(src, dst, L, es, ls, n, ns, tws, cw, tid, nt); break;
       default:
-        if constexpr (BIG)
-          fft_stage_prime<T, PAD, false>(src, dst, r, L, es, ls, n, ns, tws, cw, pl.prime, pl.poff[s], tid,
-                                  nt);
+        if constexpr (PM != PRIMES_NONE)
+          fft_stage_prime<T, PAD, PM>(src, dst, r, L, es, ls, n, ns, tws, cw, pl.prime,
+                                      pl.poff[s], tid, nt);
         break;
     }
     __syncthreads();
@@ -569,21 +569,20 @@ __device__ __forceinline__ cpx<T>* fft_fwd(cpx<T>* buf0, cpx<T>* buf1, int es, i
 // A transform length known at compile time: the radices (in the order the
 // host plan builder uses, so the twiddle table layout is the same), and with
 // them every stride, loop bound and modulus of a stage, which turns the index
-// arithmetic of the run-time engine into shifts and constants.  DynPlan<BIG>
+// arithmetic of the run-time engine into shifts and constants.  DynPlan<PM>
 // selects the run-time engine instead.
 template <int... Rs>
 struct SPlan {
   static constexpr bool dynamic = false;
   static constexpr int n = (Rs * ... * 1);
   static constexpr int nst = sizeof...(Rs);
-  static constexpr bool big = false;
 };
 
-template <bool BIG>
+template <int PM>
 struct DynPlan {
   static constexpr bool dynamic = true;
   static constexpr int n = 0;
-  static constexpr bool big = BIG;
+  static constexpr int primes = PM;
 };
 
 template <typename T, int R, int NS, int N, int L, int NT, bool PAD>
@@ -675,7 +674,8 @@ __device__ __forceinline__ cpx<T>* sfft_from(cpx<T>* src, cpx<T>* dst, int es, i
     __syncthreads();
     return dst;
   } else if constexpr (R % 2 == 1 && R > 8)  // odd primes: the cooperative stage, constant sizes
-    fft_stage_prime<T, PAD, true>(src, dst, R, L, es, ls, N, NS, tws, cw, pl.prime, pl.poff[S], tid, NT);
+    fft_stage_prime<T, PAD, PRIMES_MATRIX>(src, dst, R, L, es, ls, N, NS, tws, cw, pl.prime,
+                                           pl.poff[S], tid, NT);
   else
     sfft_stage<T, R, NS, N, L, NT, PAD>(src, dst, es, ls, tws, cw, tid);
   __syncthreads();
@@ -691,14 +691,14 @@ __device__ __forceinline__ cpx<T>* sfft(SPlan<Rs...>, cpx<T>* buf0, cpx<T>* buf1
   return sfft_from<T, L, NT, PAD, SPlan<Rs...>::n, 0, 1, Rs...>(buf0, buf1, es, ls, pl, tw, tid);
 }
 
-// Forward FFT with plan FP (SPlan<...> or DynPlan<BIG>), NT threads; same
+// Forward FFT with plan FP (SPlan<...> or DynPlan<PM>), NT threads; same
 // contract as fft_fwd.
 template <typename T, int L, int NT, bool PAD, class FP>
 __device__ __forceinline__ cpx<T>* fft_run(cpx<T>* buf0, cpx<T>* buf1, int es, int ls,
                                            const FFTPlan& pl, const cpx<T>* __restrict__ tw,
                                            int tid) {
   if constexpr (FP::dynamic)
-    return fft_fwd<T, L, FP::big, PAD>(buf0, buf1, es, ls, pl, tw, tid, NT);
+    return fft_fwd<T, L, FP::primes, PAD>(buf0, buf1, es, ls, pl, tw, tid, NT);
   else
     return sfft<T, L, NT, PAD>(FP{}, buf0, buf1, es, ls, pl, tw, tid);
 }

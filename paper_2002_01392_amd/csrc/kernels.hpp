@@ -102,6 +102,34 @@ int z_max_npr();
 size_t y_lds_bytes(int ny, int tsize, size_t elem, int lines = YL);  // LDS of one y workgroup
 size_t z_lds_bytes(const Geom& g);
 
+// The form of a plan's primes above 7 in the run-time engine: matrices (16 outputs
+// by 4 inputs at a time) where the smallest of them, R, fills them well enough, pairs
+// below that, above PRIME_MAX and where the plan has no prime table.  Where the line
+// lies depends on what else the kernel does per point; us with pairs -> matrices, FP64,
+// 128 x 120 planes (z) and 96 lines or planes of about 2e6 points (y, x):
+//   z (stage A)  R = 11 (176) 171 -> 227, 13 (208) 189 -> 239, 19 (304) 440 -> 530,
+//                23 (322) 597 -> 541, 29 (58) 91 -> 80, 47 (94) 171 -> 107
+//   y (back, dy) R = 11 (220) 98 -> 114, 13 (338) 137 -> 158, 17 (34) 91 -> 79,
+//                19 (304) 123 -> 108, 53 (106) 207 -> 102
+//   x (products) R = 11 (220) 290 -> 330, 13 (260) 321 -> 283, 47 (470) 423 -> 278
+//   x, three quantities at a time: 13 (130, three fields) 127 -> 135,
+//                17 (34) 125 -> 99, 29 (58) 245 -> 131
+//   x alone      as y
+enum PrimeUse { PF_Z, PF_Y, PF_X, PF_X3, PF_XROWS };
+inline int prime_form(const FFTPlan& pl, bool big, PrimeUse use) {
+  if (!big) return PRIMES_NONE;
+  const int least = use == PF_Z ? 23 : use == PF_X ? 13 : 17;
+  for (int s = 0; s < pl.nst; ++s)
+    if (pl.r[s] > 8 && (!pl.prime || pl.poff[s] < 0 || pl.r[s] < least)) return PRIMES_PAIRS;
+  return PRIMES_MATRIX;
+}
+#define FCNS_PM_SWITCH(FORM, CALL)                                              \
+  switch (FORM) {                                                               \
+    case PRIMES_MATRIX: { constexpr int PM = PRIMES_MATRIX; CALL; } break;      \
+    case PRIMES_PAIRS: { constexpr int PM = PRIMES_PAIRS; CALL; } break;        \
+    default: { constexpr int PM = PRIMES_NONE; CALL; } break;                   \
+  }
+
 // Dynamic LDS above 64 KiB needs an explicit per-kernel opt-in.
 #define FCNS_LAUNCH(K, GRID, BLOCK, SH, ST, ...)        \
   do {                                                  \
@@ -173,7 +201,7 @@ struct ZPassDesc {
 };
 size_t z_pass_lds(const ZArgs& a);
 long long z_pass_groups(const ZArgs& a);
-void launch_z_pass_batch(const ZPassDesc* d, int n, long long groups, int max_npr, bool big,
+void launch_z_pass_batch(const ZPassDesc* d, int n, long long groups, int max_npr, int primes,
                          size_t lds, hipStream_t st);
 // the same over problems of one N' = 32 K (z_wave_fits)
 void launch_zw_pass_batch(const ZPassDesc* d, int n, long long groups, int npr, hipStream_t st);

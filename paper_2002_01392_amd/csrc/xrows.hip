@@ -131,8 +131,8 @@ __device__ __forceinline__ int x_div(int e, int n, float rcp) {
   return q;
 }
 
-template <int LL, bool BIG>
-__global__ __launch_bounds__(XT_NT) void k_x_r2c(XArgs a, const double* __restrict__ phys,
+template <int LL, int PM>
+__global__ __launch_bounds__(XT_NT, 4) void k_x_r2c(XArgs a, const double* __restrict__ phys,
                                                  cpx<double>* __restrict__ xy, long long pfs,
                                                  long long xfs, long long nrows) {
   extern __shared__ __align__(16) char smem[];
@@ -155,7 +155,7 @@ __global__ __launch_bounds__(XT_NT) void k_x_r2c(XArgs a, const double* __restri
     Xs[2 * lds_pos<true>(rl >> 1, n, 1, ls) + (rl & 1)] = rl < have ? phys[r0 * nx + e] : 0.0;
   }
   __syncthreads();
-  const cpx<double>* R = fft_fwd<double, LL, BIG, true>(X0, X1, 1, ls, a.pl, tw, tid, XT_NT);
+  const cpx<double>* R = fft_fwd<double, LL, PM, true>(X0, X1, 1, ls, a.pl, tw, tid, XT_NT);
   const float rnk = 1.0f / (float)nkxp;
   for (int e = tid; e < LL * nkxp; e += XT_NT) {
     const int al = x_div(e, nkxp, rnk), k = e - al * nkxp;
@@ -167,8 +167,8 @@ __global__ __launch_bounds__(XT_NT) void k_x_r2c(XArgs a, const double* __restri
   }
 }
 
-template <int LL, bool BIG>
-__global__ __launch_bounds__(XT_NT) void k_x_c2r(XArgs a, const cpx<double>* __restrict__ xy,
+template <int LL, int PM>
+__global__ __launch_bounds__(XT_NT, 4) void k_x_c2r(XArgs a, const cpx<double>* __restrict__ xy,
                                                  double* __restrict__ phys, long long xfs,
                                                  long long pfs, long long nrows) {
   extern __shared__ __align__(16) char smem[];
@@ -196,7 +196,7 @@ __global__ __launch_bounds__(XT_NT) void k_x_c2r(XArgs a, const cpx<double>* __r
       X0[lds_pos<true>(al, nx - k, 1, ls)] = conj(mk(A.x + B.y, B.x - A.y));
   }
   __syncthreads();
-  const cpx<double>* R = fft_fwd<double, LL, BIG, true>(X0, X1, 1, ls, a.pl, tw, tid, XT_NT);
+  const cpx<double>* R = fft_fwd<double, LL, PM, true>(X0, X1, 1, ls, a.pl, tw, tid, XT_NT);
   const double sc = 1.0 / nx;
   const float rnx = 1.0f / (float)nx;
   for (int e = tid; e < 2 * LL * nx; e += XT_NT) {
@@ -234,14 +234,11 @@ static int x_tile_lines(int nx) { return nx <= 256 ? 8 : 4; }
     const int LL = x_tile_lines(a.nx);                                                   \
     dim3 grid((unsigned)((nrows + 2 * LL - 1) / (2 * LL)), nfields);                     \
     const size_t sh = ((size_t)a.pl.tsize + 2 * LL * x_ls(a.nx)) * sizeof(cpx<double>);  \
-    if (LL == 8 && big)                                                                  \
-      FCNS_LAUNCH((KERNEL<8, true>), grid, dim3(XT_NT), sh, st, __VA_ARGS__);            \
-    else if (LL == 8)                                                                    \
-      FCNS_LAUNCH((KERNEL<8, false>), grid, dim3(XT_NT), sh, st, __VA_ARGS__);           \
-    else if (big)                                                                        \
-      FCNS_LAUNCH((KERNEL<4, true>), grid, dim3(XT_NT), sh, st, __VA_ARGS__);            \
+    const int pm = prime_form(a.pl, big, PF_XROWS);                                      \
+    if (LL == 8)                                                                         \
+      FCNS_PM_SWITCH(pm, FCNS_LAUNCH((KERNEL<8, PM>), grid, dim3(XT_NT), sh, st, __VA_ARGS__)) \
     else                                                                                 \
-      FCNS_LAUNCH((KERNEL<4, false>), grid, dim3(XT_NT), sh, st, __VA_ARGS__);           \
+      FCNS_PM_SWITCH(pm, FCNS_LAUNCH((KERNEL<4, PM>), grid, dim3(XT_NT), sh, st, __VA_ARGS__)) \
   } while (0)
 
 void launch_x_r2c(const XArgs& a, bool big, const double* phys, cpx<double>* xy, long long pfs,

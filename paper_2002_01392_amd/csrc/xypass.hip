@@ -34,8 +34,25 @@ bool y_wide_tiles(const YArgs& a) { return a.ny == 512 && plan_is(a.pl, {8, 8, 8
 // PF: load the next tile into registers while the current one is transformed
 // (more registers, fewer waves per SIMD) or load each tile when it is needed.
 // LT lines per tile, NT threads.
+// Waves per SIMD asked of the compiler where it would otherwise take more registers
+// than they leave (matrix accumulators on top of the tile, or two tiles of 8 or 9
+// rows), and where that was faster: y back with d/dy at 96 x 300 x 69 135 -> 82 us, at
+// 2 x 127 points 213 -> 138; mixed, at 2 x 257 619 -> 354.  Not more than 9
+// rows in FP64 (2 x 307: 880 -> 1050, one workgroup per CU by its LDS anyway), nor
+// FP32 without such primes (640: 80 -> 84).
+template <typename T, class FP, int OWN>
+constexpr int y_waves() {
+  if constexpr (!FP::dynamic) {
+    return 1;
+  } else {
+    constexpr int pm = FP::primes;
+    if (sizeof(T) == 8) return OWN <= 9 && (OWN >= 8 || pm == PRIMES_MATRIX) ? 2 : 1;
+    if (pm == PRIMES_NONE || (pm == PRIMES_PAIRS && OWN < 8)) return 1;
+    return OWN <= 4 ? 4 : OWN <= 9 ? 3 : 2;
+  }
+}
 template <typename T, class FP, int OWN, bool PF, int LT, int NT>
-__global__ __launch_bounds__(NT) void k_y(YArgs a, const cpx<T>* src, cpx<T>* dst,
+__global__ __launch_bounds__(NT, (y_waves<T, FP, OWN>())) void k_y(YArgs a, const cpx<T>* src, cpx<T>* dst,
                                                cpx<T>* dst2, long long sfs, long long dfs,
                                                long long nlines, int inv, int mode) {
   constexpr int YL = LT, YNT = NT;
@@ -193,8 +210,14 @@ __device__ __forceinline__ int xp(int a, int n, int ls) { return lds_pos<true>(a
 // A workgroup of NT threads owns spectral columns k = tid + c NT and physical
 // columns n = tid + c NT (c < CC, CC NT >= nx) of its RR rows; each thread
 // loads the next pass's spectral inputs while the current pass is transformed.
+// (two waves per SIMD asked for where the matrix accumulators would leave one)
+template <class FP>
+constexpr int x_waves() {
+  if constexpr (FP::dynamic) return FP::primes == PRIMES_MATRIX ? 2 : 1;
+  return 1;
+}
 template <typename T, class FP, int RR, int NT, int CC>
-__global__ __launch_bounds__(NT) void k_x_nl(XArgs a, const cpx<T>* __restrict__ xyb,
+__global__ __launch_bounds__(NT, x_waves<FP>()) void k_x_nl(XArgs a, const cpx<T>* __restrict__ xyb,
                                              cpx<T>* __restrict__ nl, long long fs,
                                              long long nrows, int nfields) {
   constexpr int LL = RR / 2;
@@ -346,8 +369,10 @@ __device__ __forceinline__ int x3_div(int e, int n, float rcp) {
   return q;
 }
 
-template <typename T, int NF, bool BIG>
-__global__ __launch_bounds__(X3_NT) void k_x_nl3(XArgs a, const cpx<T>* __restrict__ xyb,
+// (two waves per SIMD asked for: with primes above 7 the compiler would take more than
+// 256 registers, and at 154 points, FP64, four fields, 258 us instead of 177)
+template <typename T, int NF, int PM>
+__global__ __launch_bounds__(X3_NT, 2) void k_x_nl3(XArgs a, const cpx<T>* __restrict__ xyb,
                                                  cpx<T>* __restrict__ nl, long long fs,
                                                  long long nrows) {
   extern __shared__ __align__(16) char smem[];
@@ -415,7 +440,7 @@ __global__ __launch_bounds__(X3_NT) void k_x_nl3(XArgs a, const cpx<T>* __restri
     }
     if (round < NF) load(round + 1);
     __syncthreads();
-    const cpx<T>* R = fft_fwd<T, X3_L, BIG, true>(X0, X1, 1, ls, a.pl, tw, tid, X3_NT);
+    const cpx<T>* R = fft_fwd<T, X3_L, PM, true>(X0, X1, 1, ls, a.pl, tw, tid, X3_NT);
 #pragma unroll
     for (int c = 0; c < X3_CP; ++c) {
       if (pa[c] < 0) continue;
@@ -454,7 +479,7 @@ __global__ __launch_bounds__(X3_NT) void k_x_nl3(XArgs a, const cpx<T>* __restri
             mk(acc[(L == 4 ? NF - 1 : f)][c][0], acc[(L == 4 ? NF - 1 : f)][c][1]);
     }
     __syncthreads();
-    const cpx<T>* R = fft_fwd<T, L, BIG, true>(X0, X1, 1, ls, a.pl, tw, tid, X3_NT);
+    const cpx<T>* R = fft_fwd<T, L, PM, true>(X0, X1, 1, ls, a.pl, tw, tid, X3_NT);
 #pragma unroll
     for (int c = 0; c < X3_CE; ++c) {
       if (el[c] < 0 || el[c] >= L) continue;
@@ -928,19 +953,19 @@ void launch_y(const YArgs& a, bool big, bool inv, int mode, const cpx<T>* src, c
     using P64 = SPlan<8, 8>;
     FCNS_YN(P64, 2, 8, 256);
   } else if (dyn8) {
-    if (big) {
-      if (a.ny <= 128) FCNS_YN(DynPlan<true>, 4, 8, 256);
-      else if (a.ny <= 192) FCNS_YN(DynPlan<true>, 6, 8, 256);
-      else FCNS_YN(DynPlan<true>, 9, 8, 256);
-    } else {
-      if (a.ny <= 128) FCNS_YN(DynPlan<false>, 4, 8, 256);
-      else if (a.ny <= 192) FCNS_YN(DynPlan<false>, 6, 8, 256);
-      else FCNS_YN(DynPlan<false>, 9, 8, 256);
-    }
-  } else if (big) {
-    if (a.ny <= 512) FCNS_Y(DynPlan<true>, 8); else FCNS_Y(DynPlan<true>, 16);
+    const int pm = prime_form(a.pl, big, PF_Y);
+    if (a.ny <= 128)
+      FCNS_PM_SWITCH(pm, FCNS_YN(DynPlan<PM>, 4, 8, 256))
+    else if (a.ny <= 192)
+      FCNS_PM_SWITCH(pm, FCNS_YN(DynPlan<PM>, 6, 8, 256))
+    else
+      FCNS_PM_SWITCH(pm, FCNS_YN(DynPlan<PM>, 9, 8, 256))
   } else {
-    if (a.ny <= 512) FCNS_Y(DynPlan<false>, 8); else FCNS_Y(DynPlan<false>, 16);
+    const int pm = prime_form(a.pl, big, PF_Y);
+    if (a.ny <= 512)
+      FCNS_PM_SWITCH(pm, FCNS_Y(DynPlan<PM>, 8))
+    else
+      FCNS_PM_SWITCH(pm, FCNS_Y(DynPlan<PM>, 16))
   }
 #undef FCNS_Y
 #undef FCNS_YN
@@ -969,6 +994,7 @@ bool x_reads_blocked(const XArgs& a) { return x_wave_rows(a.nx) && a.variant == 
 template <typename T>
 void launch_x_nl(const XArgs& a, bool big, const cpx<T>* xyb, cpx<T>* nl, long long fs,
                  long long nrows, int nfields, hipStream_t st) {
+  const int pm = prime_form(a.pl, big, PF_X);
   if (a.variant == 3 && a.nx <= 256) {
     // short rows: 8 rows (4 complex lines) per workgroup and one thread per
     // column (a radix-8 stage keeps half the threads busy; 4 or 16 rows, or
@@ -976,10 +1002,8 @@ void launch_x_nl(const XArgs& a, bool big, const cpx<T>* xyb, cpx<T>* nl, long l
     const int nt = (a.nx + 63) / 64 * 64;
 #define FCNS_XS(NTV)                                                                        \
   do {                                                                                      \
-    if (big)                                                                                \
-      launch_x_nl_v<T, DynPlan<true>, 8, NTV, 1>(a, xyb, nl, fs, nrows, nfields, st);       \
-    else                                                                                    \
-      launch_x_nl_v<T, DynPlan<false>, 8, NTV, 1>(a, xyb, nl, fs, nrows, nfields, st);      \
+    FCNS_PM_SWITCH(pm, (launch_x_nl_v<T, DynPlan<PM>, 8, NTV, 1>(a, xyb, nl, fs, nrows,     \
+                                                                 nfields, st)))             \
   } while (0)
     if (nt == 64)
       FCNS_XS(64);
@@ -993,10 +1017,8 @@ void launch_x_nl(const XArgs& a, bool big, const cpx<T>* xyb, cpx<T>* nl, long l
   } else if (a.variant == 2 && a.nx <= 512) {
     if (a.nx == 512 && plan_is(a.pl, {8, 8, 8}))
       launch_x_nl_v<T, SPlan<8, 8, 8>, 8, 512, 1>(a, xyb, nl, fs, nrows, nfields, st);
-    else if (big)
-      launch_x_nl_v<T, DynPlan<true>, 8, 512, 1>(a, xyb, nl, fs, nrows, nfields, st);
     else
-      launch_x_nl_v<T, DynPlan<false>, 8, 512, 1>(a, xyb, nl, fs, nrows, nfields, st);
+      FCNS_PM_SWITCH(pm, (launch_x_nl_v<T, DynPlan<PM>, 8, 512, 1>(a, xyb, nl, fs, nrows, nfields, st)))
   } else if (x_wave_rows(a.nx) && a.variant == 0) {
     // wave-level rows; enough workgroups to fill the chip several times
     const long long rpw = 64 / (a.nx / 8);
@@ -1041,24 +1063,23 @@ void launch_x_nl(const XArgs& a, bool big, const cpx<T>* xyb, cpx<T>* nl, long l
       FCNS_XW(k_x_nlw, 3, 32);
 #undef FCNS_XW
   } else if (a.variant == 0 && a.nx <= X3_MAXNX && 2 * x3_lds<T>(a) <= 160 * 1024) {
-    // (two workgroups per CU: FP64 rows up to 160 points)
+    // (two workgroups per CU, by LDS and by the registers asked for: FP64 rows up to
+    // 160 points)
     dim3 grid((unsigned)((nrows + 7) / 8));
 #define FCNS_X3(NFV, BV)                                                                      \
   FCNS_LAUNCH((k_x_nl3<T, NFV, BV>), grid, dim3(X3_NT), x3_lds<T>(a), st, a, xyb, nl, fs, nrows)
-    if (nfields == 4) {
-      if (big) FCNS_X3(4, true); else FCNS_X3(4, false);
-    } else {
-      if (big) FCNS_X3(3, true); else FCNS_X3(3, false);
-    }
+    const int pm3 = prime_form(a.pl, big, PF_X3);
+    if (nfields == 4)
+      FCNS_PM_SWITCH(pm3, FCNS_X3(4, PM))
+    else
+      FCNS_PM_SWITCH(pm3, FCNS_X3(3, PM))
 #undef FCNS_X3
   } else if (a.nx == 512 && plan_is(a.pl, {8, 8, 8}))
     launch_x_nl_v<T, SPlan<8, 8, 8>, 4, 256, 2>(a, xyb, nl, fs, nrows, nfields, st);
   else if (a.nx == 256 && plan_is(a.pl, {8, 8, 4}))
     launch_x_nl_v<T, SPlan<8, 8, 4>, 4, 256, 1>(a, xyb, nl, fs, nrows, nfields, st);
-  else if (big)
-    launch_x_nl_v<T, DynPlan<true>, 4, 256, 2>(a, xyb, nl, fs, nrows, nfields, st);
   else
-    launch_x_nl_v<T, DynPlan<false>, 4, 256, 2>(a, xyb, nl, fs, nrows, nfields, st);
+    FCNS_PM_SWITCH(pm, (launch_x_nl_v<T, DynPlan<PM>, 4, 256, 2>(a, xyb, nl, fs, nrows, nfields, st)))
 }
 template void launch_x_nl<double>(const XArgs&, bool, const cpx<double>*, cpx<double>*, long long,
                                   long long, int, hipStream_t);

@@ -317,8 +317,15 @@ __device__ __forceinline__ void check_rows(const ZArgs& a, const cpx<double> (&k
 }
 
 // continued spectral -> mixed: B_z = R o IFFT (and B_z(i k~z .) into dzdst).
+// (two waves per SIMD asked for with the matrix form: its accumulators would leave one
+// with 16 rows per thread; N' = 502 1160 -> 930 us at 128 x 120, 290 299 -> 175)
+template <class FP>
+constexpr int z_waves() {
+  if constexpr (FP::dynamic) return FP::primes == PRIMES_MATRIX ? 2 : 1;
+  return 1;
+}
 template <typename T, class FP, int OWN>
-__global__ __launch_bounds__(ZNT) void k_z_back(ZArgs a, const cpx<double>* __restrict__ src,
+__global__ __launch_bounds__(ZNT, z_waves<FP>()) void k_z_back(ZArgs a, const cpx<double>* __restrict__ src,
                                                 cpx<T>* __restrict__ dst,
                                                 cpx<T>* __restrict__ dzdst,
                                                 long long sfs, long long mfs) {
@@ -1026,12 +1033,10 @@ void launch_z_fwd(const ZArgs& a, bool big, const cpx<double>* src, cpx<double>*
     FCNS_LAUNCH((k_z_fwd<double, P288>), grid, dim3(ZNT), sh, st, a, src, dst, sfs, dfs, filter);
   else if (z_static_282(a))
     FCNS_LAUNCH((k_z_fwd<double, P282>), grid, dim3(ZNT), sh, st, a, src, dst, sfs, dfs, filter);
-  else if (big)
-    FCNS_LAUNCH((k_z_fwd<double, DynPlan<true>>), grid, dim3(ZNT), sh, st, a, src, dst, sfs, dfs,
-                filter);
   else
-    FCNS_LAUNCH((k_z_fwd<double, DynPlan<false>>), grid, dim3(ZNT), sh, st, a, src, dst, sfs, dfs,
-                filter);
+    FCNS_PM_SWITCH(prime_form(a.pl, big, PF_Z),
+                   FCNS_LAUNCH((k_z_fwd<double, DynPlan<PM>>), grid, dim3(ZNT), sh, st, a, src,
+                               dst, sfs, dfs, filter))
 }
 
 
@@ -1049,12 +1054,11 @@ void launch_z_back(const ZArgs& a, bool big, const cpx<double>* src, cpx<T>* dst
     FCNS_LAUNCH((k_z_back<T, P288, 9>), grid, dim3(ZNT), sh, st, a, src, dst, dzdst, sfs, mfs);
   } else if (z_static_282(a)) {
     FCNS_LAUNCH((k_z_back<T, P282, 9>), grid, dim3(ZNT), sh, st, a, src, dst, dzdst, sfs, mfs);
-  } else if (big) {
-    FCNS_OWN_SWITCH(own, FCNS_LAUNCH((k_z_back<T, DynPlan<true>, OWN>), grid, dim3(ZNT), sh, st,
-                                     a, src, dst, dzdst, sfs, mfs))
   } else {
-    FCNS_OWN_SWITCH(own, FCNS_LAUNCH((k_z_back<T, DynPlan<false>, OWN>), grid, dim3(ZNT), sh, st,
-                                     a, src, dst, dzdst, sfs, mfs))
+    FCNS_PM_SWITCH(prime_form(a.pl, big, PF_Z),
+                   FCNS_OWN_SWITCH(own, FCNS_LAUNCH((k_z_back<T, DynPlan<PM>, OWN>), grid,
+                                                    dim3(ZNT), sh, st, a, src, dst, dzdst, sfs,
+                                                    mfs)))
   }
 }
 template void launch_z_back<double>(const ZArgs&, bool, const cpx<double>*, cpx<double>*,
@@ -1077,12 +1081,10 @@ void launch_z_stageA(const ZArgs& a, bool big, const StageAArgs& s, int nfields,
       FCNS_LAUNCH((k_z_stageA<T, TM, P288, 9, false>), grid, dim3(ZNT), sh, st, a, s);
   } else if (z_static_282(a)) {
     FCNS_LAUNCH((k_z_stageA<T, TM, P282, 9, false>), grid, dim3(ZNT), sh, st, a, s);
-  } else if (big) {
-    FCNS_OWN_SWITCH(own, FCNS_LAUNCH((k_z_stageA<T, TM, DynPlan<true>, OWN, false>), grid, dim3(ZNT),
-                                     sh, st, a, s))
   } else {
-    FCNS_OWN_SWITCH(own, FCNS_LAUNCH((k_z_stageA<T, TM, DynPlan<false>, OWN, false>), grid,
-                                     dim3(ZNT), sh, st, a, s))
+    FCNS_PM_SWITCH(prime_form(a.pl, big, PF_Z),
+                   FCNS_OWN_SWITCH(own, FCNS_LAUNCH((k_z_stageA<T, TM, DynPlan<PM>, OWN, false>),
+                                                    grid, dim3(ZNT), sh, st, a, s)))
   }
 }
 template void launch_z_stageA<double>(const ZArgs&, bool, const StageAArgs&, int, hipStream_t);
@@ -1100,12 +1102,12 @@ void launch_z_stageB(const ZArgs& a, bool big, const StageBArgs& s, hipStream_t 
   // 128 < N' <= 288 without primes above 7 (224: 0.145 -> 0.113 ms at side
   // 192; with such primes it would leave one wave per SIMD, and 4 rows for
   // N' <= 128 measured no faster than streaming V* twice)
-  else if (big)
-    FCNS_LAUNCH((k_z_stageB<double, DynPlan<true>, 0>), grid, dim3(ZNT), sh, st, a, s);
-  else if (own == 9)
-    FCNS_LAUNCH((k_z_stageB<double, DynPlan<false>, 9>), grid, dim3(ZNT), sh, st, a, s);
+  else if (!big && own == 9)
+    FCNS_LAUNCH((k_z_stageB<double, DynPlan<PRIMES_NONE>, 9>), grid, dim3(ZNT), sh, st, a, s);
   else
-    FCNS_LAUNCH((k_z_stageB<double, DynPlan<false>, 0>), grid, dim3(ZNT), sh, st, a, s);
+    FCNS_PM_SWITCH(prime_form(a.pl, big, PF_Z),
+                   FCNS_LAUNCH((k_z_stageB<double, DynPlan<PM>, 0>), grid, dim3(ZNT), sh, st, a,
+                               s))
 }
 
 bool z_pass_fits(const ZArgs& a) { return pick_own(a.g.npr) <= 9; }
@@ -1113,20 +1115,15 @@ bool z_pass_fits(const ZArgs& a) { return pick_own(a.g.npr) <= 9; }
 size_t z_pass_lds(const ZArgs& a) { return zshared_bytes<double>(a.g, a.pl.tsize); }
 long long z_pass_groups(const ZArgs& a) { return (a.g.npen + ZPB - 1) / ZPB; }
 
-void launch_z_pass_batch(const ZPassDesc* d, int n, long long groups, int max_npr, bool big,
+void launch_z_pass_batch(const ZPassDesc* d, int n, long long groups, int max_npr, int primes,
                          size_t lds, hipStream_t st) {
   dim3 grid((unsigned)groups);
-  if (pick_own(max_npr) <= 4) {
-    if (big)
-      FCNS_LAUNCH((k_z_pass_batch<DynPlan<true>, 4>), grid, dim3(ZNT), lds, st, d, n);
-    else
-      FCNS_LAUNCH((k_z_pass_batch<DynPlan<false>, 4>), grid, dim3(ZNT), lds, st, d, n);
-  } else {
-    if (big)
-      FCNS_LAUNCH((k_z_pass_batch<DynPlan<true>, 9>), grid, dim3(ZNT), lds, st, d, n);
-    else
-      FCNS_LAUNCH((k_z_pass_batch<DynPlan<false>, 9>), grid, dim3(ZNT), lds, st, d, n);
-  }
+  if (pick_own(max_npr) <= 4)
+    FCNS_PM_SWITCH(primes, FCNS_LAUNCH((k_z_pass_batch<DynPlan<PM>, 4>), grid, dim3(ZNT), lds, st,
+                                       d, n))
+  else
+    FCNS_PM_SWITCH(primes, FCNS_LAUNCH((k_z_pass_batch<DynPlan<PM>, 9>), grid, dim3(ZNT), lds, st,
+                                       d, n))
 }
 
 void launch_z_pass(const ZArgs& a, bool big, const StageAArgs& sa, const StageBArgs& sb,
@@ -1139,20 +1136,14 @@ void launch_z_pass(const ZArgs& a, bool big, const StageAArgs& sa, const StageBA
     FCNS_LAUNCH((k_z_pass<P288, 9, false>), grid, dim3(ZNT), sh, st, a, sa, sb, zb, nfields);
   } else if (z_static_282(a)) {
     FCNS_LAUNCH((k_z_pass<P282, 9, false>), grid, dim3(ZNT), sh, st, a, sa, sb, zb, nfields);
-  } else if (big) {
-    if (own <= 4)
-      FCNS_LAUNCH((k_z_pass<DynPlan<true>, 4, false>), grid, dim3(ZNT), sh, st, a, sa, sb, zb,
-                  nfields);
-    else
-      FCNS_LAUNCH((k_z_pass<DynPlan<true>, 9, false>), grid, dim3(ZNT), sh, st, a, sa, sb, zb,
-                  nfields);
+  } else if (own <= 4) {
+    FCNS_PM_SWITCH(prime_form(a.pl, big, PF_Z),
+                   FCNS_LAUNCH((k_z_pass<DynPlan<PM>, 4, false>), grid, dim3(ZNT), sh, st, a, sa,
+                               sb, zb, nfields))
   } else {
-    if (own <= 4)
-      FCNS_LAUNCH((k_z_pass<DynPlan<false>, 4, false>), grid, dim3(ZNT), sh, st, a, sa, sb, zb,
-                  nfields);
-    else
-      FCNS_LAUNCH((k_z_pass<DynPlan<false>, 9, false>), grid, dim3(ZNT), sh, st, a, sa, sb, zb,
-                  nfields);
+    FCNS_PM_SWITCH(prime_form(a.pl, big, PF_Z),
+                   FCNS_LAUNCH((k_z_pass<DynPlan<PM>, 9, false>), grid, dim3(ZNT), sh, st, a, sa,
+                               sb, zb, nfields))
   }
 }
 
@@ -1168,14 +1159,10 @@ void launch_fc_derivative(const ZArgs& a, bool big, const double* in, double* ou
   const size_t sh = zshared_bytes<double>(a.g, a.pl.tsize);
   if (z_static_288(a))
     FCNS_LAUNCH(k_fc_derivative<P288>, grid, dim3(ZNT), sh, st, a, in, out, nlines, ps, ls, order);
-  else if (big)
-    FCNS_LAUNCH(k_fc_derivative<DynPlan<true>>, grid, dim3(ZNT), sh, st, a, in, out, nlines, ps, ls,
-                order);
   else
-    FCNS_LAUNCH(k_fc_derivative<DynPlan<false>>, grid, dim3(ZNT), sh, st, a, in, out, nlines, ps, ls,
-                order);
+    FCNS_PM_SWITCH(prime_form(a.pl, big, PF_Z),
+                   FCNS_LAUNCH(k_fc_derivative<DynPlan<PM>>, grid, dim3(ZNT), sh, st, a, in, out,
+                               nlines, ps, ls, order))
 }
-
-
 
 }  // namespace fcns

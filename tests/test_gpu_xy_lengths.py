@@ -128,3 +128,45 @@ def test_columns_of_compiled_plans(fcns, nx, ny, theta):
 @pytest.mark.parametrize("ny", [96, 192])
 def test_columns_of_compiled_plans_mixed(fcns, ny):
     test_mixed_precision_step(fcns, 12, ny)
+
+
+# both forms of prime stages on both sides of where a kernel changes from pairs to
+# matrices (13 or 17 points in x, 17 in y), beside one another in a length, and
+# above the primes with a table
+@pytest.mark.parametrize("nx,ny,theta", [
+    (22, 6, True), (26, 6, False), (34, 6, True), (220, 4, False), (242, 4, True),
+    (260, 4, True), (442, 4, False), (6, 26, False), (6, 34, True), (4, 220, True),
+    (4, 338, False), (4, 442, True), (4, 514, False)])
+def test_prime_forms(fcns, nx, ny, theta):
+    test_nonlinear_term_and_state(fcns, nx, ny, theta)
+
+
+@pytest.mark.parametrize("nx,ny", [(26, 34), (34, 26), (220, 6), (260, 8), (6, 338), (6, 526)])
+def test_prime_forms_mixed(fcns, nx, ny):
+    test_mixed_precision_step(fcns, nx, ny)
+
+
+# the same in z: 11 and 19 in pairs, 23 and 29 as matrices, for each number of rows a
+# thread holds, split and fused
+@pytest.mark.parametrize("npr", [44, 76, 92, 242, 276, 322, 338])
+def test_prime_forms_z(fcns, npr):
+    w = W.rayleigh_benard(8, 6, npr - 15, 1e5, C=15, dt=1e-3, steps=2, seed=npr, noise_rms=1e-2,
+                          kmax=2, mmax=3, perturbation="curl_eigen")
+    w = W.replace(w, dt=W.stable_dt(w))
+    v0, th0 = w.initial_state()
+    o = Oracle(Problem(**w.problem_kwargs()))
+    o.set_state(v0, th0)
+    o.rk_step(w.dt, 2)
+    rv, rth, _ = o.get_state()
+    for precision, fused, bar in (("fp64", False, 1e-11), ("fp64", True, 1e-11),
+                                  ("mixed", False, 2e-6)):
+        if fused and npr > 288:
+            continue
+        s = fcns.Solver.from_workload(w, precision=precision)
+        s.set_z_fused(fused)
+        s.set_state(torch.from_numpy(v0), torch.from_numpy(th0))
+        s.rk_step(w.dt, 2)
+        v, th, _ = s.get_state()
+        s.synchronize()
+        assert rel_l2(v, rv) < bar and rel_l2(th, rth) < bar, (precision, fused)
+        s.close()
