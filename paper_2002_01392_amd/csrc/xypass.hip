@@ -897,14 +897,15 @@ void launch_y(const YArgs& a, bool big, bool inv, int mode, const cpx<T>* src, c
   // 0.382, 0.252, 0.216 ms, mixed (three fields) 0.219, 0.160, 0.125 -> 0.167, 0.132,
   // 0.102; 128: 0.054, 0.040, 0.036 -> 0.049, 0.041, 0.033; 96: 0.027, 0.020, 0.021 ->
   // 0.024, 0.017, 0.018.  Not 192 points in FP64: three such workgroups per CU, 0.166,
-  // 0.126, 0.093 -> 0.172, 0.124, 0.100.  Above Y_DYN8 two 8-line buffers would leave
-  // one workgroup per CU.
+  // 0.126, 0.093 -> 0.172, 0.124, 0.100.  Above Y_DYN8 8 lines leave one or two
+  // workgroups per CU: 96 x 200 x 105 0.083, 0.055, 0.053 -> 0.106, 0.068, 0.068, mixed
+  // 0.047, 0.034, 0.034 -> 0.058, 0.037, 0.038.
   const bool compiled = y_wide_tiles(a) || (a.ny == 256 && plan_is(a.pl, {8, 8, 4})) ||
                         (a.ny == 192 && plan_is(a.pl, {8, 8, 3})) ||
                         (a.ny == 128 && plan_is(a.pl, {8, 8, 2})) ||
                         (a.ny == 96 && plan_is(a.pl, {8, 4, 3})) ||
                         (a.ny == 64 && plan_is(a.pl, {8, 8}));
-  constexpr int Y_DYN8 = 288;
+  constexpr int Y_DYN8 = 192;
   const bool dyn8 = !compiled && a.ny <= Y_DYN8;
   const bool c8 = compiled && a.ny < 512 && !(a.ny == 192 && sizeof(T) == 8);
   const int L = c8 || dyn8 || (a.lines == 8 && y_wide_tiles(a)) ? 8 : YL;
@@ -956,13 +957,13 @@ void launch_y(const YArgs& a, bool big, bool inv, int mode, const cpx<T>* src, c
     const int pm = prime_form(a.pl, big, PF_Y);
     if (a.ny <= 128)
       FCNS_PM_SWITCH(pm, FCNS_YN(DynPlan<PM>, 4, 8, 256))
-    else if (a.ny <= 192)
-      FCNS_PM_SWITCH(pm, FCNS_YN(DynPlan<PM>, 6, 8, 256))
     else
-      FCNS_PM_SWITCH(pm, FCNS_YN(DynPlan<PM>, 9, 8, 256))
+      FCNS_PM_SWITCH(pm, FCNS_YN(DynPlan<PM>, 6, 8, 256))
   } else {
     const int pm = prime_form(a.pl, big, PF_Y);
-    if (a.ny <= 512)
+    if (a.ny <= 256)
+      FCNS_PM_SWITCH(pm, FCNS_Y(DynPlan<PM>, 4))
+    else if (a.ny <= 512)
       FCNS_PM_SWITCH(pm, FCNS_Y(DynPlan<PM>, 8))
     else
       FCNS_PM_SWITCH(pm, FCNS_Y(DynPlan<PM>, 16))

@@ -170,3 +170,16 @@ def test_prime_forms_z(fcns, npr):
         s.synchronize()
         assert rel_l2(v, rv) < bar and rel_l2(th, rth) < bar, (precision, fused)
         s.close()
+
+
+# lengths past the last one with tiles of 8 columns (192), to the last of 4 rows per
+# thread (256) and the first of 8
+@pytest.mark.parametrize("nx,ny,theta", [(10, 180, True), (4, 194, True), (6, 200, False),
+                                         (10, 254, True), (4, 258, True), (6, 270, False)])
+def test_columns_of_any_length(fcns, nx, ny, theta):
+    test_nonlinear_term_and_state(fcns, nx, ny, theta)
+
+
+@pytest.mark.parametrize("ny", [200, 270])
+def test_columns_of_any_length_mixed(fcns, ny):
+    test_mixed_precision_step(fcns, 12, ny)
