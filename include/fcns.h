@@ -247,13 +247,15 @@ fcns_status fcns_set_slab(fcns_ctx* ctx, int32_t planes);
  * layout (it needs nx = 64, 128, 256 or 512 and the wave-level x kernel). */
 fcns_status fcns_set_blocked(fcns_ctx* ctx, int32_t on);
 
-/* Lines (kx columns) per workgroup tile of the y transforms: 4 (the
- * default) or 8 (whole 128-byte rows; ny = 512 only, else EINVAL);
- * fcns_autotune picks per launch kind.  Results are bitwise the same. */
+/* Lines (kx columns) per workgroup tile of the y transforms at ny = 512: 4
+ * (the default) or 8 (whole 128-byte rows); fcns_autotune picks per launch
+ * kind.  The tile of every other ny follows from its length (8 lines up to
+ * 192 points, except in FP64 at 192, and at 256; else 4): there 4 is accepted
+ * without effect and 8 is EINVAL.  Results are bitwise the same. */
 fcns_status fcns_set_y_lines(fcns_ctx* ctx, int32_t lines);
 
-/* The context's launch choices (y grid, prefetch and tile lines per launch
- * kind, x kernel variant, slab size, intermediate layout, fused z pass, z
+/* The context's launch choices (y grid, prefetch and, at ny = 512, tile lines
+ * per launch kind, x kernel variant, slab size, intermediate layout, fused z pass, z
  * radix order) as text, "key=value" pairs separated by ';', so that a tuned
  * configuration can be kept and applied again without autotuning.
  * fcns_get_choices writes it NUL-terminated into out (EINVAL if len is too

@@ -72,7 +72,7 @@ struct fcns_ctx {
   int ynopf = 0;
   long long ygrid1 = 0;  // y back with d/dy (two transforms per tile)
   int ynopf1 = 0;
-  int ylines = 4;        // lines (kx columns) per y tile: 4, or 8 (whole 128-byte rows)
+  int ylines = 4;        // lines (kx columns) per y tile at ny = 512: 4, or 8 (whole 128-byte rows)
   int ylines1 = 4;
   bool xyblk = false;    // rk_step's (kx, y) intermediates in the blocked layout (y back
                          // transforms write 4-column blocks contiguously; the x pass reads them)
@@ -1139,7 +1139,8 @@ extern "C" fcns_status fcns_autotune(fcns_ctx* c, char* report, int32_t report_l
     c->ylines = bl0;
     snprintf(line, sizeof(line),
              "y: grid %lld%s, %d lines (%.3f ms), with d/dy %lld%s, %d lines (%.3f ms); ", bg0,
-             bpf0 ? " no-prefetch" : "", bl0, best0, bg1, bpf1 ? " no-prefetch" : "", bl1, best1);
+             bpf0 ? " no-prefetch" : "", y_tile_lines(yargs(c, f32), f32 ? 4 : 8), best0, bg1,
+             bpf1 ? " no-prefetch" : "", y_tile_lines(yargs(c, f32, true), f32 ? 4 : 8), best1);
     rep += line;
   }
   // x pass with products: kernel variant (inputs: the y pass just run); small
@@ -1280,11 +1281,17 @@ extern "C" fcns_status fcns_autotune(fcns_ctx* c, char* report, int32_t report_l
 static std::string choices_string(const fcns_ctx* c) {
   std::string z;
   for (int s = 0; s < c->plz.nst; ++s) z += (s ? "." : "") + std::to_string(c->plz.r[s]);
+  // (the tile is a choice at ny = 512 only)
+  std::string yl, yl1;
+  if (y_wide_tiles(yargs(c))) {
+    yl = ";ylines=" + std::to_string(c->ylines);
+    yl1 = ";ylines1=" + std::to_string(c->ylines1);
+  }
   char buf[512];
   snprintf(buf, sizeof(buf),
-           "ygrid=%lld;ynopf=%d;ylines=%d;ygrid1=%lld;ynopf1=%d;ylines1=%d;xvar=%d;slab=%d;"
+           "ygrid=%lld;ynopf=%d%s;ygrid1=%lld;ynopf1=%d%s;xvar=%d;slab=%d;"
            "blocked=%d;zfused=%d;zplan=%s",
-           c->ygrid, c->ynopf, c->ylines, c->ygrid1, c->ynopf1, c->ylines1, c->xvar, c->slab,
+           c->ygrid, c->ynopf, yl.c_str(), c->ygrid1, c->ynopf1, yl1.c_str(), c->xvar, c->slab,
            c->xyblk ? 1 : 0, c->zfuse ? 1 : 0, z.c_str());
   return buf;
 }

@@ -82,10 +82,12 @@ struct YArgs {
   long long grid;    // persistent workgroups per field (0: Y_GRID)
   int noprefetch;    // 1: load each tile when needed instead of one tile ahead
   int blk;           // bit 0: src, bit 1: dst in the blocked (kx, ky) layout
-  int lines;         // lines per tile: YL, or 8 where y_wide_tiles (whole 128-byte rows)
+  int lines;         // lines per tile where y_wide_tiles: YL or 8 (whole 128-byte rows)
 };
-// 8-line tiles (512 threads) exist for the compiled 512-point plan
+// the compiled 512-point plan has tiles of both sizes to choose from
 bool y_wide_tiles(const YArgs& a);
+// the lines per tile that launch_y runs for reals of this many bytes
+int y_tile_lines(const YArgs& a, size_t real);
 
 struct XArgs {
   int nx, nkx, nkxp, ny;

@@ -29,6 +29,8 @@ size_t y_lds_bytes(int ny, int tsize, size_t elem, int lines) {
   return ((size_t)tsize + 2 * (size_t)y_span(ny, lines)) * elem;
 }
 
+constexpr int Y_DYN8 = 192;   // y_tile_lines
+
 bool y_wide_tiles(const YArgs& a) { return a.ny == 512 && plan_is(a.pl, {8, 8, 8}); }
 
 // PF: load the next tile into registers while the current one is transformed
@@ -77,8 +79,8 @@ __global__ __launch_bounds__(NT, (y_waves<T, FP, OWN>())) void k_y(YArgs a, cons
   const int npass = (mode == 1) ? 2 : 1;
   cpx<T> cur[OWN], nxt[PF ? OWN : 1];
   // XCD-aware tile order: workgroups are dispatched to the 8 XCDs in turn
-  // (workgroup b on XCD b % 8), and a tile is 4 kx columns, half of a
-  // 128-byte line, so neighbouring tiles share lines.  Each round of G tiles
+  // (workgroup b on XCD b % 8), and a tile may be less than a 128-byte line
+  // wide (4 columns; 8 in FP32), so neighbouring tiles share lines.  Each round of G tiles
   // is cut into chunks of 64; in a chunk, XCD x takes the run of 8 tiles
   // 8x .. 8x + 7, one per workgroup of that XCD, so that neighbours meet
   // their shared lines in one L2 and a partial last round still spreads
@@ -884,31 +886,37 @@ __global__ void k_sub_mean00(cpx<double>* pmix, long long npen, int nz) {
 }
 
 // ---------------------------------------------------------------- launchers
+// Compiled plans (launch_y).
+static bool y_compiled(const YArgs& a) {
+  return y_wide_tiles(a) || (a.ny == 256 && plan_is(a.pl, {8, 8, 4})) ||
+         (a.ny == 192 && plan_is(a.pl, {8, 8, 3})) || (a.ny == 128 && plan_is(a.pl, {8, 8, 2})) ||
+         (a.ny == 96 && plan_is(a.pl, {8, 4, 3})) || (a.ny == 64 && plan_is(a.pl, {8, 8}));
+}
+
+// Lines per tile: 4 or, at 512 points, 8 by choice; 8 over 256 threads for the
+// shorter compiled plans and for run-time plans up to Y_DYN8 points, whose stages
+// of ny / radix butterflies per line leave most threads idle with 4 lines (at 84
+// points 48 to 112 of 256, at 128 64 of 256 in a radix-8 stage), and whose tiles are
+// then whole 128-byte lines in FP64.  A channel solve of 32 x 32 x 33 with them: 1.64 -> 1.48 ms;
+// back with d/dy, back, forward at 256 x 256 x 257 with theta 0.437, 0.280, 0.219 ->
+// 0.382, 0.252, 0.216 ms, mixed (three fields) 0.219, 0.160, 0.125 -> 0.167, 0.132,
+// 0.102; 128: 0.054, 0.040, 0.036 -> 0.049, 0.041, 0.033; 96: 0.027, 0.020, 0.021 ->
+// 0.024, 0.017, 0.018.  Not 192 points in FP64: three such workgroups per CU, 0.166,
+// 0.126, 0.093 -> 0.172, 0.124, 0.100.  Above Y_DYN8 8 lines leave one or two
+// workgroups per CU: 96 x 200 x 105 0.083, 0.055, 0.053 -> 0.106, 0.068, 0.068, mixed
+// 0.047, 0.034, 0.034 -> 0.058, 0.037, 0.038.
+int y_tile_lines(const YArgs& a, size_t real) {
+  if (y_wide_tiles(a)) return a.lines == 8 ? 8 : YL;
+  if (y_compiled(a)) return a.ny == 192 && real == 8 ? YL : 8;
+  return a.ny <= Y_DYN8 ? 8 : YL;
+}
+
 template <typename T>
 void launch_y(const YArgs& a, bool big, bool inv, int mode, const cpx<T>* src, cpx<T>* dst,
               cpx<T>* dst2, long long sfs, long long dfs, int nplanes, int nfields,
               hipStream_t st) {
-  // Lines per tile: 4 or, at 512 points, 8 by choice; 8 over 256 threads for the
-  // shorter compiled plans and for run-time plans up to Y_DYN8 points, whose stages
-  // of ny / radix butterflies per line leave most threads idle with 4 lines (at 84
-  // points 48 to 112 of 256, at 128 64 of 256 in a radix-8 stage), and whose tiles are
-  // then whole 128-byte lines.  A channel solve of 32 x 32 x 33 with them: 1.64 -> 1.48 ms;
-  // back with d/dy, back, forward at 256 x 256 x 257 with theta 0.437, 0.280, 0.219 ->
-  // 0.382, 0.252, 0.216 ms, mixed (three fields) 0.219, 0.160, 0.125 -> 0.167, 0.132,
-  // 0.102; 128: 0.054, 0.040, 0.036 -> 0.049, 0.041, 0.033; 96: 0.027, 0.020, 0.021 ->
-  // 0.024, 0.017, 0.018.  Not 192 points in FP64: three such workgroups per CU, 0.166,
-  // 0.126, 0.093 -> 0.172, 0.124, 0.100.  Above Y_DYN8 8 lines leave one or two
-  // workgroups per CU: 96 x 200 x 105 0.083, 0.055, 0.053 -> 0.106, 0.068, 0.068, mixed
-  // 0.047, 0.034, 0.034 -> 0.058, 0.037, 0.038.
-  const bool compiled = y_wide_tiles(a) || (a.ny == 256 && plan_is(a.pl, {8, 8, 4})) ||
-                        (a.ny == 192 && plan_is(a.pl, {8, 8, 3})) ||
-                        (a.ny == 128 && plan_is(a.pl, {8, 8, 2})) ||
-                        (a.ny == 96 && plan_is(a.pl, {8, 4, 3})) ||
-                        (a.ny == 64 && plan_is(a.pl, {8, 8}));
-  constexpr int Y_DYN8 = 192;
-  const bool dyn8 = !compiled && a.ny <= Y_DYN8;
-  const bool c8 = compiled && a.ny < 512 && !(a.ny == 192 && sizeof(T) == 8);
-  const int L = c8 || dyn8 || (a.lines == 8 && y_wide_tiles(a)) ? 8 : YL;
+  const int L = y_tile_lines(a, sizeof(T));
+  const bool compiled = y_compiled(a);
   const long long nlines = (long long)nplanes * a.nkxp;
   const long long ntiles = (nlines + L - 1) / L;
   const size_t sh = y_lds_bytes(a.ny, a.pl.tsize, sizeof(cpx<T>), L);
@@ -953,7 +961,7 @@ void launch_y(const YArgs& a, bool big, bool inv, int mode, const cpx<T>* src, c
   } else if (compiled) {
     using P64 = SPlan<8, 8>;
     FCNS_YN(P64, 2, 8, 256);
-  } else if (dyn8) {
+  } else if (L == 8) {
     const int pm = prime_form(a.pl, big, PF_Y);
     if (a.ny <= 128)
       FCNS_PM_SWITCH(pm, FCNS_YN(DynPlan<PM>, 4, 8, 256))

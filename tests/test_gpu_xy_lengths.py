@@ -183,3 +183,24 @@ def test_columns_of_any_length(fcns, nx, ny, theta):
 @pytest.mark.parametrize("ny", [200, 270])
 def test_columns_of_any_length_mixed(fcns, ny):
     test_mixed_precision_step(fcns, 12, ny)
+
+
+# what is reported of the y tiles is what runs: a choice at 512 points only
+@pytest.mark.parametrize("ny,precision,lines", [(84, "fp64", 8), (192, "fp64", 4),
+                                                (192, "mixed", 8), (200, "fp64", 4),
+                                                (256, "fp64", 8), (512, "fp64", None)])
+def test_reported_columns_per_tile(fcns, ny, precision, lines):
+    s = fcns.Solver(8, ny, 11, 2.0, 3.0, 1.3, 0.01, C=15, precision=precision)
+    s.set_state(torch.zeros(3, 11, ny, 8, dtype=torch.float64))
+    report = s.autotune()
+    s.synchronize()
+    text = s.choices()
+    if lines:
+        assert report.count(f" {lines} lines") == 2 and report.count(" lines") == 2
+        assert "ylines" not in text
+    else:
+        assert "ylines=" in text and "ylines1=" in text
+    s.set_choices(text + ";ylines=4;ylines1=4")   # as a text saved before may hold
+    s.set_choices(text)
+    assert s.choices() == text
+    s.close()
