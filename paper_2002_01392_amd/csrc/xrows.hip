@@ -4,9 +4,11 @@
 //
 // Bound by memory: each row is read and written once.  Lengths of the wavefront
 // transforms (x_wave_rows) keep a row pair in registers, 8 points per lane,
-// with no workgroup barrier; other lengths go through LDS tiles with as many lines as
-// fill 256 threads in the radix stages (8 lines up to 256 points, 4 above: the
-// 4 lines x 512 threads they replace left 5 of 6 threads idle at 160 points).
+// with no workgroup barrier; other lengths go through LDS tiles: 8 lines over 256
+// threads up to 256 points (4 lines over 512 left 5 of 6 threads idle at 160 points in
+// the radix stages), 4 lines over 512 above, where 256 threads have too few rows in
+// flight (set_state at 500 x 128 x 97 485 us with 512 threads, 549 with 256; no
+// difference up to 320 points).
 // Projection of 160 x 160 x 161, which has four of them: 730 -> 624 us; filtered
 // nonlinear term of 256 x 192 x 129: 1.61 -> 1.36 ms.
 #include "kernels.hpp"
@@ -119,9 +121,9 @@ __global__ __launch_bounds__(64 * XW_WAVES) void k_xw_c2r(XArgs a,
 }
 
 // ---------------------------------------------------------------- LDS tiles
-// LL complex lines (2 LL rows) per workgroup of XT_NT threads; element n of line
+// LL complex lines (2 LL rows) per workgroup of xt_threads(LL); element n of line
 // l at lds_pos<true>(l, n, 1, x_ls(nx)).
-constexpr int XT_NT = 256;
+constexpr int xt_threads(int lines) { return lines == 8 ? 256 : 512; }
 
 // e / n for 0 <= e < 2^20 (rcp = 1 / n): the float quotient is off by at most one
 __device__ __forceinline__ int x_div(int e, int n, float rcp) {
@@ -132,9 +134,10 @@ __device__ __forceinline__ int x_div(int e, int n, float rcp) {
 }
 
 template <int LL, int PM>
-__global__ __launch_bounds__(XT_NT, 4) void k_x_r2c(XArgs a, const double* __restrict__ phys,
+__global__ __launch_bounds__(xt_threads(LL), 4) void k_x_r2c(XArgs a, const double* __restrict__ phys,
                                                  cpx<double>* __restrict__ xy, long long pfs,
                                                  long long xfs, long long nrows) {
+  constexpr int XT_NT = xt_threads(LL);
   extern __shared__ __align__(16) char smem[];
   const int tid = threadIdx.x;
   const int nx = a.nx, nkx = a.nkx, nkxp = a.nkxp, ls = x_ls(nx);
@@ -168,9 +171,10 @@ __global__ __launch_bounds__(XT_NT, 4) void k_x_r2c(XArgs a, const double* __res
 }
 
 template <int LL, int PM>
-__global__ __launch_bounds__(XT_NT, 4) void k_x_c2r(XArgs a, const cpx<double>* __restrict__ xy,
+__global__ __launch_bounds__(xt_threads(LL), 4) void k_x_c2r(XArgs a, const cpx<double>* __restrict__ xy,
                                                  double* __restrict__ phys, long long xfs,
                                                  long long pfs, long long nrows) {
+  constexpr int XT_NT = xt_threads(LL);
   extern __shared__ __align__(16) char smem[];
   const int tid = threadIdx.x;
   const int nx = a.nx, nkx = a.nkx, nkxp = a.nkxp, ls = x_ls(nx);
@@ -236,9 +240,9 @@ static int x_tile_lines(int nx) { return nx <= 256 ? 8 : 4; }
     const size_t sh = ((size_t)a.pl.tsize + 2 * LL * x_ls(a.nx)) * sizeof(cpx<double>);  \
     const int pm = prime_form(a.pl, big, PF_XROWS);                                      \
     if (LL == 8)                                                                         \
-      FCNS_PM_SWITCH(pm, FCNS_LAUNCH((KERNEL<8, PM>), grid, dim3(XT_NT), sh, st, __VA_ARGS__)) \
+      FCNS_PM_SWITCH(pm, FCNS_LAUNCH((KERNEL<8, PM>), grid, dim3(xt_threads(8)), sh, st, __VA_ARGS__)) \
     else                                                                                 \
-      FCNS_PM_SWITCH(pm, FCNS_LAUNCH((KERNEL<4, PM>), grid, dim3(XT_NT), sh, st, __VA_ARGS__)) \
+      FCNS_PM_SWITCH(pm, FCNS_LAUNCH((KERNEL<4, PM>), grid, dim3(xt_threads(4)), sh, st, __VA_ARGS__)) \
   } while (0)
 
 void launch_x_r2c(const XArgs& a, bool big, const double* phys, cpx<double>* xy, long long pfs,

@@ -40,7 +40,7 @@ def _kernels(elf):
         desc = p + 12 + (namesz + 3) // 4 * 4
         meta = msgpack.unpackb(elf[desc:desc + descsz], strict_map_key=False)
         for k in meta["amdhsa.kernels"]:
-            yield k[".name"], k[".vgpr_count"]
+            yield k[".name"], (k[".vgpr_count"], k[".max_flat_workgroup_size"])
 
 
 @pytest.fixture(scope="module")
@@ -63,4 +63,12 @@ def test_waves_per_simd(registers, kernel, least):
     got = {n: v for n, v in registers.items() if re.search(r"4fcns\d+" + kernel, n)}
     assert got, kernel
     most = {2: 256, 3: 168}[least]
-    assert not {n: v for n, v in got.items() if v > most}
+    assert not {n: v for n, (v, _) in got.items() if v > most}
+
+
+@pytest.mark.parametrize("lines,threads", [(8, 256), (4, 512)])
+def test_threads_of_the_x_tiles(registers, lines, threads):
+    # rows above 256 points have half the lines, and twice the threads, per tile
+    got = {n: t for n, (_, t) in registers.items()
+           if re.search(rf"4fcns\d+k_x_(r2c|c2r)ILi{lines}E", n)}
+    assert len(got) == 6 and set(got.values()) == {threads}
