@@ -675,13 +675,23 @@ template <typename T, int NF, int N>
 constexpr bool x_direct() {
   return N == 192 || N == 128 || (N == 256 && (NF == 3 || sizeof(T) == 4));
 }
+// And do so few workgroups gain by it?  Not FP64 rows of 128 points while two
+// workgroups per CU hold them all (2600 rows, three fields 18.6 us plain, 20.1 direct;
+// 7720: 28.0, 29.7), nor three FP32 fields at 128 or 256 points where three per CU, which
+// the buffers of the direct form rule out, do in one round (or little more) what two do
+// in two (256: 6240 rows 26.1, 29.0, 7720 27.5, 30.2; 128: 9312 rows 21.2, 22.9).
+template <typename T, int NF, int N>
+static bool x_direct_pays(long long groups) {
+  if (sizeof(T) == 8) return N != 128 || groups > 512;
+  return NF == 4 || N == 192 || groups <= 512 || groups > (N == 256 ? 1024 : 768);
+}
 
-// (two waves per SIMD asked for explicitly where the compiler would otherwise go past
-// 256 registers)
-template <typename T, int NF, int N, bool BLK>
-__global__ __launch_bounds__(64 * XW_WAVES, (N == 192 || N == 128 || N == 96 || x_direct<T, NF, N>()) ? 2 : 1) void k_x_nlw(XArgs a, const cpx<T>* __restrict__ xyb,
-                                                         cpx<T>* __restrict__ nl, long long fs,
-                                                         long long nrows) {
+// DMA: direct loads.  (Two waves per SIMD asked for explicitly where the compiler would
+// otherwise go past 256 registers.)
+template <typename T, int NF, int N, bool BLK, bool DMA>
+__global__ __launch_bounds__(64 * XW_WAVES, (N == 192 || N == 128 || N == 96 || DMA) ? 2 : 1)
+void k_x_nlw(XArgs a, const cpx<T>* __restrict__ xyb, cpx<T>* __restrict__ nl, long long fs,
+             long long nrows) {
   // Three or four fields: pairs of real quantities per complex transform,
   // each spectral slot read once: (u, du/dx), (v, dv/dx), (w, dw/dx) from
   // one load each (the x derivative is i k~x times the same coefficients),
@@ -693,11 +703,12 @@ __global__ __launch_bounds__(64 * XW_WAVES, (N == 192 || N == 128 || N == 96 || 
   constexpr int NP = NF == 4 ? 8 : 6;
   constexpr int TH = NF - 1;  // theta's accumulator (four fields)
   constexpr int S = N / 8, RPW = 64 / S;  // lanes per row, rows per wave
-  constexpr bool DMA = x_direct<T, NF, N>();
   constexpr int EPL = 16 / sizeof(cpx<T>);                   // elements per direct load
   constexpr int NI = (RPW * N / 2 / EPL + 63) / 64;          // direct loads per slot
   constexpr int PB = 64 * EPL * NI;                          // elements of one slot
-  __shared__ cpx<T> tw[N == 512 ? XW_TW : (N <= 64 ? 7 : 14) * S];
+  // (without direct loads no LDS is short, and at 64 points in FP32 the rows behind a table
+  // of just its size took 16.0 us instead of 15.0)
+  __shared__ cpx<T> tw[DMA ? 14 * S : XW_TW];
   __shared__ cpx<T> xbuf[XW_WAVES * XW_BUF];
   __shared__ cpx<T> pre[DMA ? XW_WAVES : 1][DMA ? 2 * PB + 64 * EPL : 1];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -708,7 +719,13 @@ __global__ __launch_bounds__(64 * XW_WAVES, (N == 192 || N == 128 || N == 96 || 
   const bool spare = lane >= S * RPW;
   const int ln = spare ? lane - S : lane;
   const int t = ln % S, half = ln / S;
-  const XwBuf<T> buf{xbuf, wv * XW_BUF + half * (XW_BUF / RPW)};
+  const auto buf = [&] {
+    const int o = wv * XW_BUF + half * (XW_BUF / RPW);
+    if constexpr (DMA)
+      return XwBuf<T>{xbuf, o};
+    else
+      return xbuf + o;
+  }();
   const int nkxp = a.nkxp;
   const T kxs = (T)a.kxs;
   const T sc = T(1) / T(N);
@@ -984,6 +1001,22 @@ template void launch_y<double>(const YArgs&, bool, bool, int, const cpx<double>*
 template void launch_y<float>(const YArgs&, bool, bool, int, const cpx<float>*, cpx<float>*,
                               cpx<float>*, long long, long long, int, int, hipStream_t);
 
+template <typename T, int NF, int N>
+static void launch_x_nlw(const XArgs& a, dim3 grid, const cpx<T>* xyb, cpx<T>* nl, long long fs,
+                         long long nrows, hipStream_t st) {
+#define FCNS_XD(BLKV, DMAV)                                                                 \
+  FCNS_LAUNCH((k_x_nlw<T, NF, N, BLKV, DMAV>), grid, dim3(64 * XW_WAVES), 0, st, a, xyb, nl, \
+              fs, nrows)
+  if constexpr (x_direct<T, NF, N>()) {
+    if (x_direct_pays<T, NF, N>(grid.x)) {
+      if (a.blk_in) FCNS_XD(true, true); else FCNS_XD(false, true);
+      return;
+    }
+  }
+  if (a.blk_in) FCNS_XD(true, false); else FCNS_XD(false, false);
+#undef FCNS_XD
+}
+
 template <typename T, class FP, int RR, int NT, int CC>
 static void launch_x_nl_v(const XArgs& a, const cpx<T>* xyb, cpx<T>* nl, long long fs,
                           long long nrows, int nfields, hipStream_t st) {
@@ -1033,43 +1066,39 @@ void launch_x_nl(const XArgs& a, bool big, const cpx<T>* xyb, cpx<T>* nl, long l
     const long long rpw = 64 / (a.nx / 8);
     const long long need = (nrows + rpw * XW_WAVES - 1) / (rpw * XW_WAVES);
     dim3 grid((unsigned)(need < 4096 ? need : 4096));
-#define FCNS_XW(K, NFV, NV)                                                                  \
-  do {                                                                                      \
-    if (a.blk_in)                                                                           \
-      FCNS_LAUNCH((K<T, NFV, NV, true>), grid, dim3(64 * XW_WAVES), 0, st, a, xyb, nl, fs,   \
-                  nrows);                                                                   \
-    else                                                                                    \
-      FCNS_LAUNCH((K<T, NFV, NV, false>), grid, dim3(64 * XW_WAVES), 0, st, a, xyb, nl, fs,  \
-                  nrows);                                                                   \
-  } while (0)
+#define FCNS_XW(NFV, NV) launch_x_nlw<T, NFV, NV>(a, grid, xyb, nl, fs, nrows, st)
     if (a.nx == 512 && nfields == 4)
-      FCNS_XW(k_x_nlw, 4, 512);
+      FCNS_XW(4, 512);
+    else if (a.nx == 512 && a.blk_in)
+      FCNS_LAUNCH((k_x_nlw_q<T, 3, 512, true>), grid, dim3(64 * XW_WAVES), 0, st, a, xyb, nl, fs,
+                  nrows);
     else if (a.nx == 512)
-      FCNS_XW(k_x_nlw_q, 3, 512);
+      FCNS_LAUNCH((k_x_nlw_q<T, 3, 512, false>), grid, dim3(64 * XW_WAVES), 0, st, a, xyb, nl, fs,
+                  nrows);
     else if (a.nx == 256 && nfields == 4)
-      FCNS_XW(k_x_nlw, 4, 256);
+      FCNS_XW(4, 256);
     else if (a.nx == 256)
-      FCNS_XW(k_x_nlw, 3, 256);
+      FCNS_XW(3, 256);
     else if (a.nx == 192 && nfields == 4)
-      FCNS_XW(k_x_nlw, 4, 192);
+      FCNS_XW(4, 192);
     else if (a.nx == 192)
-      FCNS_XW(k_x_nlw, 3, 192);
+      FCNS_XW(3, 192);
     else if (a.nx == 128 && nfields == 4)
-      FCNS_XW(k_x_nlw, 4, 128);
+      FCNS_XW(4, 128);
     else if (a.nx == 128)
-      FCNS_XW(k_x_nlw, 3, 128);
+      FCNS_XW(3, 128);
     else if (a.nx == 96 && nfields == 4)
-      FCNS_XW(k_x_nlw, 4, 96);
+      FCNS_XW(4, 96);
     else if (a.nx == 96)
-      FCNS_XW(k_x_nlw, 3, 96);
+      FCNS_XW(3, 96);
     else if (a.nx == 64 && nfields == 4)
-      FCNS_XW(k_x_nlw, 4, 64);
+      FCNS_XW(4, 64);
     else if (a.nx == 64)
-      FCNS_XW(k_x_nlw, 3, 64);
+      FCNS_XW(3, 64);
     else if (nfields == 4)
-      FCNS_XW(k_x_nlw, 4, 32);
+      FCNS_XW(4, 32);
     else
-      FCNS_XW(k_x_nlw, 3, 32);
+      FCNS_XW(3, 32);
 #undef FCNS_XW
   } else if (a.variant == 0 && a.nx <= X3_MAXNX && 2 * x3_lds<T>(a) <= 160 * 1024) {
     // (two workgroups per CU, by LDS and by the registers asked for: FP64 rows up to

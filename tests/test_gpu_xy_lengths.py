@@ -204,3 +204,11 @@ def test_reported_columns_per_tile(fcns, ny, precision, lines):
     s.set_choices(text)
     assert s.choices() == text
     s.close()
+
+
+# the same lengths where few workgroups run without direct loads
+@pytest.mark.parametrize("nx,ny,nz,theta,precision", [
+    (128, 66, 65, True, "fp64"), (128, 66, 65, False, "fp64"), (128, 96, 97, False, "mixed"),
+    (256, 96, 65, False, "mixed")])
+def test_rows_not_loaded_ahead(fcns, nx, ny, nz, theta, precision):
+    test_rows_loaded_ahead(fcns, nx, ny, nz, theta, precision)
