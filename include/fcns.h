@@ -291,9 +291,10 @@ fcns_status fcns_get_wall_grad(fcns_ctx* ctx, double* out);
 /* Kernel timing for tracing and roofline reports.  While enabled, every
  * kernel that rk_step launches is bracketed by HIP events recorded on the
  * context stream (small extra launch latency).  Classes: y_back_dy,
- * y_back_dz, x_nl, y_fwd, z_stageA, z_stageB, z_back, z_pass, xy_slabs.  The
- * one launch of small planes counts once in each of the first four, its time
- * divided by the transforms they stand for (2 : 1 : 4 : 1). */
+ * y_back_dz, x_nl, y_fwd, z_stageA, z_stageB, z_back, z_pass, xy_slabs,
+ * plane_nl.  plane_nl is the one launch that does the work of the first four
+ * on planes of 32 or 64 by 32 or 64 points; each of those reports the same
+ * launch, whole, where it runs (a sum over classes leaves them out then). */
 fcns_status fcns_set_timing(fcns_ctx* ctx, int32_t enable);
 /* The same for a subset: bit i of mask enables class i (in the order above;
  * 0 disables timing).  Bits beyond the last class: FCNS_EINVAL.  Fewer

@@ -515,7 +515,7 @@ class Solver:
         self._keep = (fs, wg)
 
     TIMING_CLASSES = ("y_back_dy", "y_back_dz", "x_nl", "y_fwd", "z_stageA", "z_stageB",
-                      "z_back", "z_pass", "xy_slabs")
+                      "z_back", "z_pass", "xy_slabs", "plane_nl")
 
     def set_timing(self, enable=True, classes=None):
         """Event-time rk_step's kernels: every class, or only those named in
@@ -532,7 +532,9 @@ class Solver:
         self._check(self.lib.fcns_timing_reset(self.ctx))
 
     def timing_report(self):
-        """{kernel class: (launches, total ms)} since the last reset."""
+        """{kernel class: (launches, total ms)} since the last reset.  Where
+        plane_nl ran (planes of 32 or 64 by 32 or 64 points), the four y and x
+        classes report that same launch."""
         n = ctypes.c_int32()
         names = ctypes.create_string_buffer(32 * 16)
         counts = (ctypes.c_int64 * 16)()

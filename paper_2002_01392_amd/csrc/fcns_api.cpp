@@ -101,16 +101,16 @@ struct fcns_ctx {
 
 // Kernel classes timed by fcns_set_timing.
 enum { T_YBACK_DY = 0, T_YBACK_DZ, T_XNL, T_YFWD, T_ZSTAGEA, T_ZSTAGEB, T_ZBACK, T_ZPASS,
-       T_XYSLAB, T_NCLS };
+       T_XYSLAB, T_PLANE, T_NCLS };
 static const char* kTimingNames[T_NCLS] = {"y_back_dy", "y_back_dz", "x_nl", "y_fwd",
                                            "z_stageA", "z_stageB", "z_back", "z_pass",
-                                           "xy_slabs"};
-// The launch of small planes does the work of the four y and x classes: its time
-// is divided among them by the one-dimensional transforms each stands for (of
-// eight per field), and counts as a launch of each.
-enum { T_PLANE = T_NCLS };
-static const int kPlaneShare[4] = {2, 1, 4, 1};   // y_back_dy, y_back_dz, x_nl, y_fwd
-static const uint32_t kPlaneMask = 1u << T_YBACK_DY | 1u << T_YBACK_DZ | 1u << T_XNL | 1u << T_YFWD;
+                                           "xy_slabs", "plane_nl"};
+// The launch of small planes does the work of four other classes too: each of
+// them that is timed reports it whole.
+static uint32_t class_mask(int cls) {
+  if (cls != T_PLANE) return 1u << cls;
+  return 1u << T_PLANE | 1u << T_YBACK_DY | 1u << T_YBACK_DZ | 1u << T_XNL | 1u << T_YFWD;
+}
 
 static void timing_flush(fcns_ctx* c) {
   if (c->recs.empty()) return;
@@ -118,16 +118,12 @@ static void timing_flush(fcns_ctx* c) {
   for (const auto& r : c->recs) {
     float ms = 0.f;
     if (hipEventElapsedTime(&ms, r.a, r.b) == hipSuccess) {
-      if (r.cls == T_PLANE) {
-        for (int k = 0; k < 4; ++k)
-          if ((c->tmask >> k) & 1u) {
-            c->tms[k] += ms * kPlaneShare[k] / 8;
-            c->tcnt[k] += 1;
-          }
-        continue;
-      }
-      c->tms[r.cls] += ms;
-      c->tcnt[r.cls] += 1;
+      const uint32_t m = c->tmask & class_mask(r.cls);
+      for (int k = 0; k < T_NCLS; ++k)
+        if ((m >> k) & 1u) {
+          c->tms[k] += ms;
+          c->tcnt[k] += 1;
+        }
     }
   }
   c->recs.clear();
@@ -136,7 +132,7 @@ static void timing_flush(fcns_ctx* c) {
 
 static void tbeg(fcns_ctx* c, int cls) {
   c->cur.cls = -1;
-  if (!c->timing || !(c->tmask & (cls == T_PLANE ? kPlaneMask : 1u << cls))) return;
+  if (!c->timing || !(c->tmask & class_mask(cls))) return;
   if (c->evnext + 2 > c->evpool.size()) timing_flush(c);
   c->cur.cls = cls;
   c->cur.a = c->evpool[c->evnext++];

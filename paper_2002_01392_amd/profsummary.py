@@ -28,7 +28,8 @@ HERE = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 
 # kernel name prefix -> timing class of the library (the y kernel serves three
 # classes of equal traffic pattern; it is reported as one)
-CLASSES = {"fcns::k_x_nl<": "x_nl", "fcns::k_x_nlw<": "x_nl", "fcns::k_x_nlw_q<": "x_nl",
+CLASSES = {"fcns::k_x_nl<": "x_nl", "fcns::k_x_nl3<": "x_nl", "fcns::k_x_nlw<": "x_nl",
+           "fcns::k_x_nlw_q<": "x_nl", "fcns::k_plane_nl<": "plane_nl",
            "fcns::k_z_stageA<": "z_stageA", "fcns::k_z_stageB<": "z_stageB",
            "fcns::k_z_back<": "z_back", "fcns::k_z_pass<": "z_pass", "fcns::k_zw_pass<": "z_pass",
            "fcns::k_zw_back<": "z_back", "fcns::k_y<": "y"}

@@ -85,3 +85,27 @@ def test_step_and_replays(fcns, nx, ny, nz, C, precision, bar):
         rv, rth, _ = o.get_state()
         assert rel_l2(v, rv) < bar and rel_l2(th, rth) < bar
     s.close()
+
+
+def test_launch_time_is_reported_whole(fcns):
+    # in its own class, and the same launches in each of the four whose work it does
+    w = W.channel(32, 32, 33, 1500.0, C=25, dt=1e-3, steps=1, seed=61, noise_rms=0.02)
+    v0, _ = w.initial_state()
+    s = fcns.Solver.from_workload(w)
+    s.set_state(torch.from_numpy(v0))
+    s.rk_step(w.dt, 1)
+    s.set_timing(True)
+    s.timing_reset()
+    s.rk_step(w.dt, 3)
+    rep = s.timing_report()
+    assert rep["plane_nl"][0] == 6 and rep["plane_nl"][1] > 0
+    for k in ("y_back_dy", "y_back_dz", "x_nl", "y_fwd"):
+        assert rep[k] == rep["plane_nl"]
+    for k in ("plane_nl", "x_nl"):
+        s.set_timing(True, classes=[k])
+        s.timing_reset()
+        s.rk_step(w.dt, 2)
+        one = s.timing_report()
+        assert one[k][0] == 4 and one[k][1] > 0
+        assert all(n == 0 for c, (n, _) in one.items() if c != k)
+    s.close()
