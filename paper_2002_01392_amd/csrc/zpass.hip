@@ -914,8 +914,10 @@ __device__ __forceinline__ void z_pass_group(const ZLds<double>& L, const ZArgs&
   }
 }
 
+// (three waves per SIMD asked for with 5 rows per thread: two more registers cost 27 us
+// of 116 at N' = 160)
 template <class FP, int OWN, bool WV>
-__global__ __launch_bounds__(ZNT, 2) void k_z_pass(ZArgs a, StageAArgs sa, StageBArgs sb,
+__global__ __launch_bounds__(ZNT, OWN == 5 ? 3 : 2) void k_z_pass(ZArgs a, StageAArgs sa, StageBArgs sb,
                                                    ZBackArgs zb, int nf) {
   extern __shared__ __align__(16) char smem[];
   __shared__ cpx<double> coef[ZPB * 5];
@@ -1131,11 +1133,34 @@ void launch_z_pass(const ZArgs& a, bool big, const StageAArgs& sa, const StageBA
   dim3 grid((unsigned)((a.g.npen + ZPB - 1) / ZPB));
   const size_t sh = zshared_bytes<double>(a.g, a.pl.tsize);
   const int own = pick_own(a.g.npr);
-  // (N' = 32 K with the stored tables runs launch_zw_pass instead)
+  // (N' = 32 K runs launch_zw_pass with the stored tables, and these compiled plans with
+  // tables of C + d > 64 or d > 7: at 96 x 96 with (8, 31) N' = 64 57 us, 128 94, 160 116,
+  // 224 191, against 125, 171, 204 and 271 with the run-time engine)
   if (z_static_288(a)) {
-    FCNS_LAUNCH((k_z_pass<P288, 9, false>), grid, dim3(ZNT), sh, st, a, sa, sb, zb, nfields);
+    bool wv = true;  // W is V^t for every field (the first RK stage)
+    for (int f = 0; f < nfields; ++f) wv = wv && sa.w[f] == sa.vt[f];
+    if (wv)
+      FCNS_LAUNCH((k_z_pass<P288, 9, true>), grid, dim3(ZNT), sh, st, a, sa, sb, zb, nfields);
+    else
+      FCNS_LAUNCH((k_z_pass<P288, 9, false>), grid, dim3(ZNT), sh, st, a, sa, sb, zb, nfields);
   } else if (z_static_282(a)) {
     FCNS_LAUNCH((k_z_pass<P282, 9, false>), grid, dim3(ZNT), sh, st, a, sa, sb, zb, nfields);
+  } else if (own == 9 && plan_is(a.pl, {8, 4, 7})) {
+    // N' / 32 rows per thread
+    FCNS_LAUNCH((k_z_pass<SPlan<8, 4, 7>, 7, false>), grid, dim3(ZNT), sh, st, a, sa, sb, zb,
+                nfields);
+  } else if (own == 9 && plan_is(a.pl, {8, 4, 5})) {
+    FCNS_LAUNCH((k_z_pass<SPlan<8, 4, 5>, 5, false>), grid, dim3(ZNT), sh, st, a, sa, sb, zb,
+                nfields);
+  } else if (own == 4 && plan_is(a.pl, {8, 8, 2})) {
+    FCNS_LAUNCH((k_z_pass<SPlan<8, 8, 2>, 4, false>), grid, dim3(ZNT), sh, st, a, sa, sb, zb,
+                nfields);
+  } else if (own == 4 && plan_is(a.pl, {8, 4, 3})) {
+    FCNS_LAUNCH((k_z_pass<SPlan<8, 4, 3>, 3, false>), grid, dim3(ZNT), sh, st, a, sa, sb, zb,
+                nfields);
+  } else if (own == 4 && plan_is(a.pl, {8, 8})) {
+    FCNS_LAUNCH((k_z_pass<SPlan<8, 8>, 2, false>), grid, dim3(ZNT), sh, st, a, sa, sb, zb,
+                nfields);
   } else if (own <= 4) {
     FCNS_PM_SWITCH(prime_form(a.pl, big, PF_Z),
                    FCNS_LAUNCH((k_z_pass<DynPlan<PM>, 4, false>), grid, dim3(ZNT), sh, st, a, sa,

@@ -60,7 +60,9 @@ def _oracle(w, v0, th0):
     return o.get_state()[:2]
 
 
-@pytest.mark.parametrize("npr,d,C", [(128, 8, 31), (288, 5, 63)])
+# (64 to 224: a compiled plan each in the fused pass, as 288)
+@pytest.mark.parametrize("npr,d,C", [(128, 8, 31), (288, 5, 63), (64, 8, 31), (96, 8, 31),
+                                     (160, 5, 63), (192, 8, 31), (224, 5, 63)])
 def test_step_and_batch(fcns, npr, d, C):
     w = _workload(npr, d, C, 870)
     v0, th0 = w.initial_state()

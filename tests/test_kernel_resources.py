@@ -57,6 +57,7 @@ def registers():
     (r"k_yId.*DynPlan.*Li[4689]ELb[01]ELi[48]E.*", 2),  # y transforms of up to 512 points
     ("k_z_backId.*DynPlan.*", 2),                       # z back transforms
     ("k_z_(back|stageA)Id.*DynPlan.*Li4E.*", 3),        # N' <= 128
+    ("k_z_passI.*SPlan.*ELi[2-5]ELb0E.*", 3),            # compiled plans of N' <= 160
     (r"k_z_stageBId.*DynPlanIL[bi]\dEEELi0E.*", 3),
 ])
 def test_waves_per_simd(registers, kernel, least):
