@@ -1480,7 +1480,7 @@ static void batch_descriptors(fcns_batch* b, std::vector<ZPassDesc>& h) {
     bk.groups += z_pass_groups(a);
     bk.max_npr = std::max(bk.max_npr, c->g.npr);
     // (pairs run any plan, matrices those that all take them)
-    const int form = prime_form(a.pl, c->big_z, PF_Z);
+    const int form = prime_form(a.pl, c->big_z, ZPB, ZNT, true);
     if (form != PRIMES_NONE)
       bk.primes = bk.primes == PRIMES_NONE || bk.primes == form ? form : PRIMES_PAIRS;
     bk.lds = std::max(bk.lds, z_pass_lds(a));

@@ -489,8 +489,8 @@ __device__ __forceinline__ void prime_matrix(const cpx<T>* __restrict__ src,
 
 constexpr int PRIME_PG = 5;
 
-// How a plan's primes above 7 are transformed (prime_form chooses): a kernel holds
-// one form only, as the matrix accumulators would cost the other's occupancy.
+// How a plan's primes above 7 are transformed (prime_form of kernels.hpp chooses): a
+// kernel holds one form only, as the matrix accumulators would cost the other's occupancy.
 enum { PRIMES_NONE = 0, PRIMES_PAIRS = 1, PRIMES_MATRIX = 2 };
 
 template <typename T, bool PAD, int PM>

@@ -104,26 +104,33 @@ int z_max_npr();
 size_t y_lds_bytes(int ny, int tsize, size_t elem, int lines = YL);  // LDS of one y workgroup
 size_t z_lds_bytes(const Geom& g);
 
-// The form of a plan's primes above 7 in the run-time engine: matrices (16 outputs
-// by 4 inputs at a time) where the smallest of them, R, fills them well enough, pairs
-// below that, above PRIME_MAX and where the plan has no prime table.  Where the line
-// lies depends on what else the kernel does per point; us with pairs -> matrices, FP64,
-// 128 x 120 planes (z) and 96 lines or planes of about 2e6 points (y, x):
-//   z (stage A)  R = 11 (176) 171 -> 227, 13 (208) 189 -> 239, 19 (304) 440 -> 530,
-//                23 (322) 597 -> 541, 29 (58) 91 -> 80, 47 (94) 171 -> 107
-//   y (back, dy) R = 11 (220) 98 -> 114, 13 (338) 137 -> 158, 17 (34) 91 -> 79,
-//                19 (304) 123 -> 108, 53 (106) 207 -> 102
-//   x (products) R = 11 (220) 290 -> 330, 13 (260) 321 -> 283, 47 (470) 423 -> 278
-//   x, three quantities at a time: 13 (130, three fields) 127 -> 135,
-//                17 (34) 125 -> 99, 29 (58) 245 -> 131
-//   x alone      as y
-enum PrimeUse { PF_Z, PF_Y, PF_X, PF_X3, PF_XROWS };
-inline int prime_form(const FFTPlan& pl, bool big, PrimeUse use) {
+// The form of a plan's primes above 7 in the run-time engine, for `lines` lines over
+// `threads` threads: matrices where their products, 16 outputs by 4 input pairs at a time
+// and a whole round of the wavefronts at least, take fewer rounds than the pairs' multiply-
+// adds (counted in whole rounds of the threads, five pairs per item, or one where there
+// are few: 0.4 of the time of five).  The ratio of the two predicts what was measured,
+// us with pairs -> matrices, FP64, 96 lines or planes of about 2e6 points (y, x) and
+// 128 x 120 planes (z, stage A):
+//   y (back, dy) 94 = 2 x 47 (0.33) 208 -> 104, 58 (0.71) 113 -> 92, 274 (0.75) 221 -> 161,
+//                130 (1.00) 112 -> 112, 208 (1.33) 112 -> 123, 220 (2.00) 97 -> 114
+//   x (products) 310 (0.33) 442 -> 240, 470 (0.65) 437 -> 278, 338 (0.83) 449 -> 361,
+//                220 (2.00) 301 -> 330
+//   z            94 (0.65) 171 -> 107, 158 (0.51) 313 -> 257, 322 (0.55) 597 -> 541, 310
+//                (0.80) 484 -> 494, 222 (0.83) 252 -> 282, 176 (1.60) 171 -> 227
+// z has more of its time elsewhere, where the accumulators' registers cost: from 0.75.
+inline int prime_form(const FFTPlan& pl, bool big, int lines, int threads, bool z = false) {
   if (!big) return PRIMES_NONE;
-  const int least = use == PF_Z ? 23 : use == PF_X ? 13 : 17;
-  for (int s = 0; s < pl.nst; ++s)
-    if (pl.r[s] > 8 && (!pl.prime || pl.poff[s] < 0 || pl.r[s] < least)) return PRIMES_PAIRS;
-  return PRIMES_MATRIX;
+  auto rounds = [](int items, int per) { return (items + per - 1) / per; };
+  int matrix = 0, pairs = 0;
+  for (int s = 0; s < pl.nst; ++s) {
+    const int R = pl.r[s], H = (R - 1) / 2, nb = lines * (pl.n / R), five = (H + 4) / 5;
+    if (R <= 8) continue;
+    if (!pl.prime || pl.poff[s] < 0) return PRIMES_PAIRS;
+    matrix += 10 * rounds(prime_tiles(R) * rounds(2 * nb, 16), threads / 64) * prime_steps(R);
+    pairs += 2 * nb * five >= threads ? 10 * rounds(nb * five, threads) * H
+                                      : 4 * rounds(nb * (H + 1), threads) * H;
+  }
+  return (z ? 4 * matrix <= 3 * pairs : matrix < pairs) ? PRIMES_MATRIX : PRIMES_PAIRS;
 }
 #define FCNS_PM_SWITCH(FORM, CALL)                                              \
   switch (FORM) {                                                               \

@@ -238,7 +238,7 @@ static int x_tile_lines(int nx) { return nx <= 256 ? 8 : 4; }
     const int LL = x_tile_lines(a.nx);                                                   \
     dim3 grid((unsigned)((nrows + 2 * LL - 1) / (2 * LL)), nfields);                     \
     const size_t sh = ((size_t)a.pl.tsize + 2 * LL * x_ls(a.nx)) * sizeof(cpx<double>);  \
-    const int pm = prime_form(a.pl, big, PF_XROWS);                                      \
+    const int pm = prime_form(a.pl, big, LL, xt_threads(LL));                            \
     if (LL == 8)                                                                         \
       FCNS_PM_SWITCH(pm, FCNS_LAUNCH((KERNEL<8, PM>), grid, dim3(xt_threads(8)), sh, st, __VA_ARGS__)) \
     else                                                                                 \

@@ -979,13 +979,13 @@ void launch_y(const YArgs& a, bool big, bool inv, int mode, const cpx<T>* src, c
     using P64 = SPlan<8, 8>;
     FCNS_YN(P64, 2, 8, 256);
   } else if (L == 8) {
-    const int pm = prime_form(a.pl, big, PF_Y);
+    const int pm = prime_form(a.pl, big, L, YNT);
     if (a.ny <= 128)
       FCNS_PM_SWITCH(pm, FCNS_YN(DynPlan<PM>, 4, 8, 256))
     else
       FCNS_PM_SWITCH(pm, FCNS_YN(DynPlan<PM>, 6, 8, 256))
   } else {
-    const int pm = prime_form(a.pl, big, PF_Y);
+    const int pm = prime_form(a.pl, big, L, YNT);
     if (a.ny <= 256)
       FCNS_PM_SWITCH(pm, FCNS_Y(DynPlan<PM>, 4))
     else if (a.ny <= 512)
@@ -1036,12 +1036,12 @@ bool x_reads_blocked(const XArgs& a) { return x_wave_rows(a.nx) && a.variant == 
 template <typename T>
 void launch_x_nl(const XArgs& a, bool big, const cpx<T>* xyb, cpx<T>* nl, long long fs,
                  long long nrows, int nfields, hipStream_t st) {
-  const int pm = prime_form(a.pl, big, PF_X);
   if (a.variant == 3 && a.nx <= 256) {
     // short rows: 8 rows (4 complex lines) per workgroup and one thread per
     // column (a radix-8 stage keeps half the threads busy; 4 or 16 rows, or
     // 4 rows over 256 threads, measured slower)
     const int nt = (a.nx + 63) / 64 * 64;
+    const int pm = prime_form(a.pl, big, 4, nt);
 #define FCNS_XS(NTV)                                                                        \
   do {                                                                                      \
     FCNS_PM_SWITCH(pm, (launch_x_nl_v<T, DynPlan<PM>, 8, NTV, 1>(a, xyb, nl, fs, nrows,     \
@@ -1060,7 +1060,8 @@ void launch_x_nl(const XArgs& a, bool big, const cpx<T>* xyb, cpx<T>* nl, long l
     if (a.nx == 512 && plan_is(a.pl, {8, 8, 8}))
       launch_x_nl_v<T, SPlan<8, 8, 8>, 8, 512, 1>(a, xyb, nl, fs, nrows, nfields, st);
     else
-      FCNS_PM_SWITCH(pm, (launch_x_nl_v<T, DynPlan<PM>, 8, 512, 1>(a, xyb, nl, fs, nrows, nfields, st)))
+      FCNS_PM_SWITCH(prime_form(a.pl, big, 4, 512),
+                     (launch_x_nl_v<T, DynPlan<PM>, 8, 512, 1>(a, xyb, nl, fs, nrows, nfields, st)))
   } else if (x_wave_rows(a.nx) && a.variant == 0) {
     // wave-level rows; enough workgroups to fill the chip several times
     const long long rpw = 64 / (a.nx / 8);
@@ -1106,18 +1107,19 @@ void launch_x_nl(const XArgs& a, bool big, const cpx<T>* xyb, cpx<T>* nl, long l
     dim3 grid((unsigned)((nrows + 7) / 8));
 #define FCNS_X3(NFV, BV)                                                                      \
   FCNS_LAUNCH((k_x_nl3<T, NFV, BV>), grid, dim3(X3_NT), x3_lds<T>(a), st, a, xyb, nl, fs, nrows)
-    const int pm3 = prime_form(a.pl, big, PF_X3);
+    const int pm = prime_form(a.pl, big, X3_L, X3_NT);
     if (nfields == 4)
-      FCNS_PM_SWITCH(pm3, FCNS_X3(4, PM))
+      FCNS_PM_SWITCH(pm, FCNS_X3(4, PM))
     else
-      FCNS_PM_SWITCH(pm3, FCNS_X3(3, PM))
+      FCNS_PM_SWITCH(pm, FCNS_X3(3, PM))
 #undef FCNS_X3
   } else if (a.nx == 512 && plan_is(a.pl, {8, 8, 8}))
     launch_x_nl_v<T, SPlan<8, 8, 8>, 4, 256, 2>(a, xyb, nl, fs, nrows, nfields, st);
   else if (a.nx == 256 && plan_is(a.pl, {8, 8, 4}))
     launch_x_nl_v<T, SPlan<8, 8, 4>, 4, 256, 1>(a, xyb, nl, fs, nrows, nfields, st);
   else
-    FCNS_PM_SWITCH(pm, (launch_x_nl_v<T, DynPlan<PM>, 4, 256, 2>(a, xyb, nl, fs, nrows, nfields, st)))
+    FCNS_PM_SWITCH(prime_form(a.pl, big, 2, 256),
+                   (launch_x_nl_v<T, DynPlan<PM>, 4, 256, 2>(a, xyb, nl, fs, nrows, nfields, st)))
 }
 template void launch_x_nl<double>(const XArgs&, bool, const cpx<double>*, cpx<double>*, long long,
                                   long long, int, hipStream_t);

@@ -1036,7 +1036,7 @@ void launch_z_fwd(const ZArgs& a, bool big, const cpx<double>* src, cpx<double>*
   else if (z_static_282(a))
     FCNS_LAUNCH((k_z_fwd<double, P282>), grid, dim3(ZNT), sh, st, a, src, dst, sfs, dfs, filter);
   else
-    FCNS_PM_SWITCH(prime_form(a.pl, big, PF_Z),
+    FCNS_PM_SWITCH(prime_form(a.pl, big, ZPB, ZNT, true),
                    FCNS_LAUNCH((k_z_fwd<double, DynPlan<PM>>), grid, dim3(ZNT), sh, st, a, src,
                                dst, sfs, dfs, filter))
 }
@@ -1057,7 +1057,7 @@ void launch_z_back(const ZArgs& a, bool big, const cpx<double>* src, cpx<T>* dst
   } else if (z_static_282(a)) {
     FCNS_LAUNCH((k_z_back<T, P282, 9>), grid, dim3(ZNT), sh, st, a, src, dst, dzdst, sfs, mfs);
   } else {
-    FCNS_PM_SWITCH(prime_form(a.pl, big, PF_Z),
+    FCNS_PM_SWITCH(prime_form(a.pl, big, ZPB, ZNT, true),
                    FCNS_OWN_SWITCH(own, FCNS_LAUNCH((k_z_back<T, DynPlan<PM>, OWN>), grid,
                                                     dim3(ZNT), sh, st, a, src, dst, dzdst, sfs,
                                                     mfs)))
@@ -1084,7 +1084,7 @@ void launch_z_stageA(const ZArgs& a, bool big, const StageAArgs& s, int nfields,
   } else if (z_static_282(a)) {
     FCNS_LAUNCH((k_z_stageA<T, TM, P282, 9, false>), grid, dim3(ZNT), sh, st, a, s);
   } else {
-    FCNS_PM_SWITCH(prime_form(a.pl, big, PF_Z),
+    FCNS_PM_SWITCH(prime_form(a.pl, big, ZPB, ZNT, true),
                    FCNS_OWN_SWITCH(own, FCNS_LAUNCH((k_z_stageA<T, TM, DynPlan<PM>, OWN, false>),
                                                     grid, dim3(ZNT), sh, st, a, s)))
   }
@@ -1107,7 +1107,7 @@ void launch_z_stageB(const ZArgs& a, bool big, const StageBArgs& s, hipStream_t 
   else if (!big && own == 9)
     FCNS_LAUNCH((k_z_stageB<double, DynPlan<PRIMES_NONE>, 9>), grid, dim3(ZNT), sh, st, a, s);
   else
-    FCNS_PM_SWITCH(prime_form(a.pl, big, PF_Z),
+    FCNS_PM_SWITCH(prime_form(a.pl, big, ZPB, ZNT, true),
                    FCNS_LAUNCH((k_z_stageB<double, DynPlan<PM>, 0>), grid, dim3(ZNT), sh, st, a,
                                s))
 }
@@ -1162,11 +1162,11 @@ void launch_z_pass(const ZArgs& a, bool big, const StageAArgs& sa, const StageBA
     FCNS_LAUNCH((k_z_pass<SPlan<8, 8>, 2, false>), grid, dim3(ZNT), sh, st, a, sa, sb, zb,
                 nfields);
   } else if (own <= 4) {
-    FCNS_PM_SWITCH(prime_form(a.pl, big, PF_Z),
+    FCNS_PM_SWITCH(prime_form(a.pl, big, ZPB, ZNT, true),
                    FCNS_LAUNCH((k_z_pass<DynPlan<PM>, 4, false>), grid, dim3(ZNT), sh, st, a, sa,
                                sb, zb, nfields))
   } else {
-    FCNS_PM_SWITCH(prime_form(a.pl, big, PF_Z),
+    FCNS_PM_SWITCH(prime_form(a.pl, big, ZPB, ZNT, true),
                    FCNS_LAUNCH((k_z_pass<DynPlan<PM>, 9, false>), grid, dim3(ZNT), sh, st, a, sa,
                                sb, zb, nfields))
   }
@@ -1185,7 +1185,7 @@ void launch_fc_derivative(const ZArgs& a, bool big, const double* in, double* ou
   if (z_static_288(a))
     FCNS_LAUNCH(k_fc_derivative<P288>, grid, dim3(ZNT), sh, st, a, in, out, nlines, ps, ls, order);
   else
-    FCNS_PM_SWITCH(prime_form(a.pl, big, PF_Z),
+    FCNS_PM_SWITCH(prime_form(a.pl, big, ZPB, ZNT, true),
                    FCNS_LAUNCH(k_fc_derivative<DynPlan<PM>>, grid, dim3(ZNT), sh, st, a, in, out,
                                nlines, ps, ls, order))
 }

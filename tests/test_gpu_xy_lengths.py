@@ -130,12 +130,11 @@ def test_columns_of_compiled_plans_mixed(fcns, ny):
     test_mixed_precision_step(fcns, 12, ny)
 
 
-# both forms of prime stages on both sides of where a kernel changes from pairs to
-# matrices (13 or 17 points in x, 17 in y), beside one another in a length, and
-# above the primes with a table
+# both forms of prime stages (pairs, matrices) in every kernel that has them, two
+# primes in a length, and above the primes with a table
 @pytest.mark.parametrize("nx,ny,theta", [
     (22, 6, True), (26, 6, False), (34, 6, True), (220, 4, False), (242, 4, True),
-    (260, 4, True), (442, 4, False), (6, 26, False), (6, 34, True), (4, 220, True),
+    (260, 4, True), (442, 4, False), (6, 26, False), (6, 34, True), (6, 110, True), (4, 220, True),
     (4, 338, False), (4, 442, True), (4, 514, False)])
 def test_prime_forms(fcns, nx, ny, theta):
     test_nonlinear_term_and_state(fcns, nx, ny, theta)
@@ -146,8 +145,8 @@ def test_prime_forms_mixed(fcns, nx, ny):
     test_mixed_precision_step(fcns, nx, ny)
 
 
-# the same in z: 11 and 19 in pairs, 23 and 29 as matrices, for each number of rows a
-# thread holds, split and fused
+# the same in z, for each number of rows a thread holds, split and fused: pairs at 44,
+# 242 and 338, matrices at 76, 92, 276 and 322
 @pytest.mark.parametrize("npr", [44, 76, 92, 242, 276, 322, 338])
 def test_prime_forms_z(fcns, npr):
     w = W.rayleigh_benard(8, 6, npr - 15, 1e5, C=15, dt=1e-3, steps=2, seed=npr, noise_rms=1e-2,
