@@ -402,10 +402,11 @@ __device__ __forceinline__ void prime_outputs(const cpx<T>* __restrict__ src,
 // (k = 0: X_0 = P_0).  A wavefront forms 16 k of 16 columns by 16 x 16 x 4 products, the
 // roots from a table through L1, the inputs from LDS once; the two parts of a
 // butterfly sit in neighbouring lanes and exchange their Q.  The pair form reads five
-// roots and two inputs from LDS for twenty multiply-adds and is bound by LDS.  Fused
-// z pass at 256 x 256 x 257 (6 x 47) 1.55 -> 1.29 ms; stage A and back transforms at
-// 160 x 160 x 161 (6 x 31) 0.406 -> 0.343 and 0.253 -> 0.209 ms, at 120 x 84 x 81 (2 x 53)
-// 0.144 -> 0.102 and 0.095 -> 0.064.
+// roots and two inputs from LDS for twenty multiply-adds and is bound by LDS.  Pair
+// form -> this one: fused z pass at 256 x 256 x 257 (6 x 47) 1.48 -> 1.22 ms (its stages
+// apart are even); stage A and back transforms at 160 x 160 x 161 (6 x 31) 0.264 ->
+// 0.248 and 0.169 -> 0.147 ms, at 120 x 84 x 81 (2 x 53, with theta) 0.133 -> 0.079 and
+// 0.084 -> 0.047.
 typedef double v4d __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 template <typename T>
@@ -617,7 +618,7 @@ __device__ __forceinline__ void sfft_stage(const cpx<T>* __restrict__ src, cpx<T
 // (a < R2, nrt = n / (R1 R2), a multiple of ns) write what the R2-point butterflies
 // (j - k) R1 + k + m ns (m < R1) read.  Saves a pass over LDS and a barrier; the
 // arithmetic is that of the two stages.  6 x 47: fused z pass at 256 x 256 x 257
-// 1.29 -> 1.23 ms.  Not in the run-time engine, where its registers cost every other
+// 1.29 -> 1.22 ms.  Not in the run-time engine, where its registers cost every other
 // length more (x pass at 120 points 0.075 -> 0.128 ms).
 template <typename T, int R1, int R2, int NS, int N, int L, int NT, bool PAD>
 __device__ __forceinline__ void sfft_stage2(const cpx<T>* __restrict__ src, cpx<T>* __restrict__ dst,

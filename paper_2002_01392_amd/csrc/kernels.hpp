@@ -23,6 +23,14 @@ inline bool x_wave_rows(int nx) {
   return nx == 512 || nx == 256 || nx == 192 || nx == 128 || nx == 96 || nx == 64 || nx == 32;
 }
 
+// e / n for 0 <= e < 2^20 (rcp = 1 / n): the float quotient is off by at most one
+__device__ __forceinline__ int x_div(int e, int n, float rcp) {
+  int q = (int)((float)e * rcp);
+  if (q * n > e) --q;
+  if (q * n + n <= e) ++q;
+  return q;
+}
+
 // Does the run-time plan have exactly these radices (in this order)?
 inline bool plan_is(const FFTPlan& pl, std::initializer_list<int> rs) {
   if (pl.nst != (int)rs.size()) return false;

@@ -34,8 +34,10 @@ __global__ __launch_bounds__(256) void k_fc_extend(const double* __restrict__ in
 // are one lane each (rows i = lane of [M_r | M_l], held in registers across the
 // lines for the d of the stored tables); the 2 d boundary points are loaded
 // once, one per lane, and broadcast through scalar registers.
-// 50001 lines of 193 + 25 points, a call at a time on changing inputs: 257 -> 49 us
-// (3.4 TB/s of the 164 MB it moves; a large copy runs at 4.9).
+// 50001 lines of 193 + 25 points (164 MB; the cache holds 256), against the thread per
+// line: eight pairs of buffers in turn 256 -> 49 us (3.4 TB/s; a large copy runs at
+// 4.9), one pair again and again 163 -> 32; one call after 1 GiB of other reads 258 ->
+// 41, of other writes, which have to leave the cache first, 290 -> 62.
 constexpr int EXT_U = 4;
 constexpr int EXT_NT = 256;
 

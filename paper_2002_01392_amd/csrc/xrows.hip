@@ -125,14 +125,6 @@ __global__ __launch_bounds__(64 * XW_WAVES) void k_xw_c2r(XArgs a,
 // l at lds_pos<true>(l, n, 1, x_ls(nx)).
 constexpr int xt_threads(int lines) { return lines == 8 ? 256 : 512; }
 
-// e / n for 0 <= e < 2^20 (rcp = 1 / n): the float quotient is off by at most one
-__device__ __forceinline__ int x_div(int e, int n, float rcp) {
-  int q = (int)((float)e * rcp);
-  if (q * n > e) --q;
-  if (q * n + n <= e) ++q;
-  return q;
-}
-
 template <int LL, int PM>
 __global__ __launch_bounds__(xt_threads(LL), 4) void k_x_r2c(XArgs a, const double* __restrict__ phys,
                                                  cpx<double>* __restrict__ xy, long long pfs,

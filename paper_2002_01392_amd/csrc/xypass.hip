@@ -363,14 +363,6 @@ static size_t x3_lds(const XArgs& a) {
   return ((size_t)a.pl.tsize + 2 * X3_L * x_ls(a.nx)) * sizeof(cpx<T>);
 }
 
-// e / n for 0 <= e < 2^20 (rcp = 1 / n): the float quotient is off by at most one
-__device__ __forceinline__ int x3_div(int e, int n, float rcp) {
-  int q = (int)((float)e * rcp);
-  if (q * n > e) --q;
-  if (q * n + n <= e) ++q;
-  return q;
-}
-
 // (two waves per SIMD asked for: with primes above 7 the compiler would take more than
 // 256 registers, and at 154 points, FP64, four fields, 258 us instead of 177)
 template <typename T, int NF, int PM>
@@ -394,7 +386,7 @@ __global__ __launch_bounds__(X3_NT, 2) void k_x_nl3(XArgs a, const cpx<T>* __res
 #pragma unroll
   for (int c = 0; c < X3_CE; ++c) {
     const int e = tid + c * X3_NT;
-    el[c] = x3_div(e, nkxp, rnk);
+    el[c] = x_div(e, nkxp, rnk);
     ek[c] = e - el[c] * nkxp;
     if (el[c] >= X3_L || ek[c] >= nkx) el[c] = -1;
   }
@@ -403,7 +395,7 @@ __global__ __launch_bounds__(X3_NT, 2) void k_x_nl3(XArgs a, const cpx<T>* __res
 #pragma unroll
   for (int c = 0; c < X3_CP; ++c) {
     const int e = tid + c * X3_NT;
-    pa[c] = x3_div(e, nx, rnx);
+    pa[c] = x_div(e, nx, rnx);
     pn[c] = e - pa[c] * nx;
     if (pa[c] >= 4) pa[c] = -1;
   }
